@@ -131,46 +131,137 @@ __device__ __forceinline__ float fq_value(unsigned long long v) {
     return (float)((double)(long long)v * (1.0 / kFqScale));
 }
 
+// Has the compiler load these (uniform) values where it stands, in one batch
+// of scalar loads, instead of each beside its first use.
+__device__ __forceinline__ void wanted() {}
+template <typename T, typename... U>
+__device__ __forceinline__ void wanted(T v, U... u) {
+#ifdef __AMDGCN__
+    __asm__ volatile("" ::"s"(v));
+#else
+    (void)v;
+#endif
+    wanted(u...);
+}
+
 // One cell's collision in deviation form (eqs. LBE, f^eq, S_i,
 // hydro_var1/2), in two parts so that callers can store each population as
-// soon as it is relaxed: Moments takes the streamed deviations f_i - w_i and
-// the force (half-force velocity); relax() gives post-collision population
-// i: BGK towards the second-order equilibrium plus the Guo source.
-template <int DIM>
+// soon as it is relaxed: the constructor takes the streamed deviations
+// f_i - w_i and the force (half-force velocity); relax() hands every
+// post-collision population to out(i, value): BGK towards the second-order
+// equilibrium plus, with FORCED, the Guo source.
+//
+// A wavefront issues about 250 vector instructions per D2Q9 cell update (330
+// before) and its chain from the last load to the first store is as long as
+// they are: a lattice that fits the caches (1024x512) waits for that chain,
+// the 256-droplet fp16 batch for issue slots.  So no term of a zero velocity
+// component is formed (0 u + v is v, but the compiler has to keep it: u may
+// be infinite) and the two populations of an opposite pair share c.U and
+// (c.U)^2.  Every operation and its rounding is written out (contraction is
+// off), so that the result does not depend on the kernel that the code is
+// inlined into: the products of the sums below are rounded once, inside the
+// fma that takes them.  With the record of the droplet read in one batch
+// (k_lb): 1024x512 fp32 15.7 -> 13.9 us per coupled step, the batch 245 ->
+// 236 us.
+// Keeps the narrowing of v to fp16 a rounding of its own (the compiler would
+// merge it into the fma before it).
+__device__ __forceinline__ float unfused(float v) {
+#ifdef __AMDGCN__
+    __asm__("" : "+v"(v));
+#endif
+    return v;
+}
+
+template <int DIM, int S>
 struct Moments {
-    float drho, rho, ux, uy, uz, usq, uF, Fx, Fy, Fz;
+    float drho, rho, inv, jx, jy, jz, ux, uy, uz, usq, Fx, Fy, Fz;
     __device__ __forceinline__ Moments(const float* f, float fx, float fy, float fz) : Fx(fx), Fy(fy), Fz(fz) {
+#pragma clang fp contract(off)
         using L = Lattice<DIM>;
-        float jx = 0.f, jy = 0.f, jz = 0.f;
-        drho = 0.f;
+        jx = jy = jz = uz = 0.f;
+        drho = f[0];
 #pragma unroll
-        for (int i = 0; i < L::Q; ++i) {
+        for (int i = 1; i < L::Q; ++i) {
             drho += f[i];
             if (L::c[i][0] > 0) jx += f[i]; else if (L::c[i][0] < 0) jx -= f[i];
             if (L::c[i][1] > 0) jy += f[i]; else if (L::c[i][1] < 0) jy -= f[i];
             if (DIM == 3) { if (L::c[i][2] > 0) jz += f[i]; else if (L::c[i][2] < 0) jz -= f[i]; }
         }
         rho = 1.f + drho;
-        const float inv = 1.f / rho;
-        ux = (jx + 0.5f * Fx) * inv;
-        uy = (jy + 0.5f * Fy) * inv;
-        uz = DIM == 3 ? (jz + 0.5f * Fz) * inv : 0.f;
-        usq = ux * ux + uy * uy + uz * uz;
-        uF = ux * Fx + uy * Fy + uz * Fz;
+        inv = 1.f / rho;
+        jx = __builtin_fmaf(0.5f, Fx, jx);
+        jy = __builtin_fmaf(0.5f, Fy, jy);
+        ux = jx * inv;
+        uy = jy * inv;
+        usq = DIM == 3 ? __builtin_fmaf(ux, ux, uy * uy) : __builtin_fmaf(uy, uy, ux * ux);
+        if (DIM == 3) {
+            jz = __builtin_fmaf(0.5f, Fz, jz);
+            uz = jz * inv;
+            usq = __builtin_fmaf(uz, uz, usq);
+        }
     }
-    __device__ __forceinline__ float relax(int i, float fi, float om, float g, bool forced) const {
+    // c_i . U.  With fp32 and fp16 storage the last component of a diagonal
+    // enters as the unrounded product j / rho; with bf16 as the rounded u.
+    static constexpr bool kFused = S != ST_BF16;
+    __device__ __forceinline__ float dot_u(int i) const {
+#pragma clang fp contract(off)
         using L = Lattice<DIM>;
         const int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
-        const float cu = cx * ux + cy * uy + (DIM == 3 ? cz * uz : 0.f);
-        // f_eq - w = w (rho - 1) + w rho (3 cu + 4.5 cu^2 - 1.5 u^2)
-        const float feq = L::w[i] * (drho + rho * (3.f * cu + 4.5f * cu * cu - 1.5f * usq));
-        float v = fi - om * (fi - feq);
-        if (forced) {
-            const float cF = cx * Fx + cy * Fy + (DIM == 3 ? cz * Fz : 0.f);
-            // S_i = (1 - 1/2tau) w_i [3 (c - U).F + 9 (c.U)(c.F)]
-            v += g * L::w[i] * (3.f * (cF - uF) + 9.f * cu * cF);
+        const float sx = cx < 0 ? -ux : ux, sy = cy < 0 ? -uy : uy, sz = cz < 0 ? -uz : uz;
+        if (DIM == 3 && cz != 0) {
+            if (cx == 0 && cy == 0) return sz;
+            const float o = cx != 0 ? sx : sy;
+            return kFused ? __builtin_fmaf(cz < 0 ? -inv : inv, jz, o) : o + sz;
         }
-        return v;
+        if (cy == 0) return sx;
+        if (cx == 0) return sy;
+        if (!kFused) return sx + sy;
+        // 3D: (-1, -1) carries x unrounded, the others y; 2D: (-1, 1) y, the others x
+        if (DIM == 3 ? cx < 0 && cy < 0 : !(cx < 0 && cy > 0))
+            return __builtin_fmaf(cx < 0 ? -inv : inv, jx, sy);
+        return __builtin_fmaf(cy < 0 ? -inv : inv, jy, sx);
+    }
+    __device__ __forceinline__ float dot_f(int i) const {
+        using L = Lattice<DIM>;
+        const int cx = L::c[i][0], cy = L::c[i][1], cz = L::c[i][2];
+        const float sx = cx < 0 ? -Fx : Fx, sy = cy < 0 ? -Fy : Fy, sz = cz < 0 ? -Fz : Fz;
+        if (DIM == 3 && cz != 0) return cx != 0 ? sx + sz : (cy != 0 ? sy + sz : sz);
+        return cx != 0 ? (cy != 0 ? sx + sy : sx) : sy;
+    }
+    // whether c . U of i + 1 is exactly the negative of that of i (odd i)
+    static constexpr bool mirrored(int i) {
+        return !kFused || !((DIM == 3 && i == 7) || (DIM == 2 && i == 7));
+    }
+    template <bool FORCED, typename Out>
+    __device__ __forceinline__ void relax(const float* f, float om, float g, Out&& out) const {
+#pragma clang fp contract(off)
+        using L = Lattice<DIM>;
+        float uF = 0.f;
+        if (FORCED) {
+            uF = DIM == 3 ? __builtin_fmaf(ux, Fx, uy * Fy) : __builtin_fmaf(uy, Fy, ux * Fx);
+            if (DIM == 3) uF = __builtin_fmaf(uz, Fz, uF);
+        }
+        auto one = [&](int i, float cu, float q, float cF) {
+            // f_eq - w = w (rho - 1) + w rho (3 cu + 4.5 cu^2 - 1.5 u^2); q = 4.5 cu^2
+            const float e = __builtin_fmaf(rho, __builtin_fmaf(-1.5f, usq, __builtin_fmaf(3.f, cu, q)), drho);
+            float v = __builtin_fmaf(-om, __builtin_fmaf(-L::w[i], e, f[i]), f[i]);
+            if (FORCED)
+                // S_i = (1 - 1/2tau) w_i [3 (c - U).F + 9 (c.U)(c.F)]
+                v = __builtin_fmaf(g * L::w[i], __builtin_fmaf(cF, 9.f * cu, 3.f * (cF - uF)), v);
+            out(i, S == ST_F16 ? unfused(v) : v);
+        };
+        one(0, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int i = 1; i < L::Q; i += 2) {
+            const float cu = dot_u(i), q = cu * (4.5f * cu), cF = FORCED ? dot_f(i) : 0.f;
+            one(i, cu, q, cF);
+            if (mirrored(i)) {
+                one(i + 1, -cu, q, -cF);
+            } else {
+                const float cv = dot_u(i + 1);
+                one(i + 1, cv, cv * (4.5f * cv), -cF);
+            }
+        }
     }
 };
 
@@ -240,8 +331,14 @@ __global__ __launch_bounds__(kBlock) void k_lb(const DropDev* __restrict__ drops
     constexpr bool FLAT = BX == 0;
     constexpr int BY = FLAT ? 1 : kBlock / (FLAT ? 1 : BX);
     const int4 tile = tiles[blockIdx.x];  // the host lays the list out in block order
-    const DropDev& D = drops[ONE ? 0 : tile.x];
+    // The droplet's record is read as a whole at the start: read where they
+    // are used, its fields were eight scalar loads in a row, each waited for
+    // (see Moments for what it gave).
+    const DropDev D = drops[ONE ? 0 : tile.x];
     const int nx = D.nx, ny = D.ny, nz = D.nz;
+    wanted(tile.y, tile.z, tile.w, D.nx, D.ny, D.nz, D.nstrip, D.bcx, D.bcy, D.bcz, D.ncell, D.f_off, D.c_off,
+           D.flag_off, D.omega, D.guo, D.force_mode, D.fst, D.ppl, fsrc_all, fdst_all, Fq_all, U_all, flags_all,
+           flags_clr);
     int x, y, z;
     if constexpr (FLAT) {
         const int c = tile.y * kBlock + (int)threadIdx.x;
@@ -262,32 +359,57 @@ __global__ __launch_bounds__(kBlock) void k_lb(const DropDev* __restrict__ drops
     const typename C::T* __restrict__ fsrc = fsrc_all + D.f_off;
     typename C::T* __restrict__ fdst = fdst_all + D.f_off;
 
-    // source coordinates for c = +1 (xm) and c = -1 (xp); -1 marks a wall
+    // Source coordinates for c = +1 (xm) and c = -1 (xp), and whether the
+    // source lies beyond a wall: the population was reflected there, and the
+    // opposite population of this cell is taken (half-way bounce-back).
+    // 2D: wrapped coordinates and selects.  3D: -1 marks a wall; the
+    // branches that the compiler makes of it space the nineteen loads out,
+    // and 256x256x128 fp32 is 1.4 % faster with them (254.5 against 258.2 us
+    // per coupled step).
     int xm = x - 1, xp = x + 1, ym = y - 1, yp = y + 1, zm = z - 1, zp = z + 1;
-    if (xm < 0) xm = D.bcx ? -1 : nx - 1;
-    if (xp >= nx) xp = D.bcx ? -1 : 0;
-    if (ym < 0) ym = D.bcy ? -1 : ny - 1;
-    if (yp >= ny) yp = D.bcy ? -1 : 0;
-    if (DIM == 3) {
+    bool wxm = false, wxp = false, wym = false, wyp = false;
+    if constexpr (DIM == 2) {
+        const bool wx = D.bcx != 0, wy = D.bcy != 0;
+        wxm = wx & (x == 0);
+        wxp = wx & (x == nx - 1);
+        wym = wy & (y == 0);
+        wyp = wy & (y == ny - 1);
+        xm = x == 0 ? nx - 1 : xm;
+        xp = x == nx - 1 ? 0 : xp;
+        ym = y == 0 ? ny - 1 : ym;
+        yp = y == ny - 1 ? 0 : yp;
+    } else {
+        if (xm < 0) xm = D.bcx ? -1 : nx - 1;
+        if (xp >= nx) xp = D.bcx ? -1 : 0;
+        if (ym < 0) ym = D.bcy ? -1 : ny - 1;
+        if (yp >= ny) yp = D.bcy ? -1 : 0;
         if (zm < 0) zm = D.bcz ? -1 : nz - 1;
         if (zp >= nz) zp = D.bcz ? -1 : 0;
     }
 
-    // the band flag of this cell's strip is requested before the
+    // The band flag of this cell's strip is requested before the
     // populations: loads return in order, so waiting for the flag then does
     // not wait for the populations, and a band wavefront's F loads overlap
-    // them instead of following them
+    // them instead of following them.  A lone 2D droplet's kernel requests
+    // it after them: few of its wavefronts lie in the band, and the others
+    // then do not start on a line that the node kernel wrote just before
+    // (1024x512: 13.8 against 15.4 us per coupled step; the 256-droplet fp16
+    // batch 246 against 236 us).
     // A tiled wavefront reads its strips' flags as one aligned word.
     using SW = typename Strip<DIM, S>::Word;
     constexpr int SPW = Strip<DIM, S>::per64;
+    constexpr bool LATE = DIM == 2 && ONE;
     const long long fi = D.flag_off + (long long)(z * ny + y) * D.nstrip + (x >> Strip<DIM, S>::shift);
     int flag;
-    if constexpr (FLAT) {
-        flag = D.force_mode == 1 ? 1 : (int)flags_all[fi];
-    } else {
-        const SW w = D.force_mode == 1 ? ~SW(0) : *reinterpret_cast<const SW*>(flags_all + (fi & ~(long long)(SPW - 1)));
-        flag = (int)((w >> (8 * (int)(fi & (SPW - 1)))) & 0xffu);
-    }
+    auto get_flag = [&](bool given) {
+        if constexpr (FLAT) {
+            flag = given ? 1 : (int)flags_all[fi];
+        } else {
+            const SW word = given ? ~SW(0) : *reinterpret_cast<const SW*>(flags_all + (fi & ~(long long)(SPW - 1)));
+            flag = (int)((word >> (8 * (int)(fi & (SPW - 1)))) & 0xffu);
+        }
+    };
+    if (!LATE) get_flag(D.force_mode == 1);
     // Populations move through buffer instructions (32-bit lane offsets,
     // base in scalar registers): one descriptor per opposite pair (i,
     // opp(i)), based at the lower index, so that a lane offset never
@@ -302,14 +424,22 @@ __global__ __launch_bounds__(kBlock) void k_lb(const DropDev* __restrict__ drops
         const int sx = cx > 0 ? xm : (cx < 0 ? xp : x);
         const int sy = cy > 0 ? ym : (cy < 0 ? yp : y);
         const int sz = DIM == 3 ? (cz > 0 ? zm : (cz < 0 ? zp : z)) : 0;
-        // a source beyond a wall means the population was reflected there:
-        // take the opposite population of this cell (half-way bounce-back)
-        const bool wall = (sx | sy | sz) < 0;
         const int lo = i == 0 ? 0 : ((i & 1) ? i : i - 1);
         const auto rs = buffer_of(fsrc + (long long)lo * fst, (i == 0 ? 1 : 2) * fst * SB);
-        const int rel = wall ? (opp(i) - lo) * fst + pc : (i - lo) * fst + sz * ppl + sy * nx + sx;
+        int rel;
+        if constexpr (DIM == 2) {
+            bool wall = false;
+            if (cx) wall = wall | (cx > 0 ? wxm : wxp);
+            if (cy) wall = wall | (cy > 0 ? wym : wyp);
+            const int own = (opp(i) - lo) * fst + pc, from = (i - lo) * fst + sy * nx + sx;
+            rel = wall ? own : from;
+        } else {
+            const bool wall = (sx | sy | sz) < 0;
+            rel = wall ? (opp(i) - lo) * fst + pc : (i - lo) * fst + sz * ppl + sy * nx + sx;
+        }
         f[i] = C::template load_buf<NTL ? kBufNT : 0>(rs, (unsigned)rel * SB);
     }
+    if (LATE) get_flag(false);
 
     const float* __restrict__ F = F_all + (long long)DIM * D.c_off;
     unsigned long long* __restrict__ Fq = Fq_all + (long long)DIM * D.c_off;
@@ -347,7 +477,7 @@ __global__ __launch_bounds__(kBlock) void k_lb(const DropDev* __restrict__ drops
             Fz = fq_value(q2);
         }
     }
-    const Moments<DIM> M(f, Fx, Fy, Fz);
+    const Moments<DIM, S> M(f, Fx, Fy, Fz);
     const float rho = M.rho, ux = M.ux, uy = M.uy, uz = M.uz;
     float om = D.omega, g = D.guo;
     if (VIS && D.visc) {
@@ -361,13 +491,17 @@ __global__ __launch_bounds__(kBlock) void k_lb(const DropDev* __restrict__ drops
         // for the crossings of the next step
         if (x == 0 && xclr) xclr[D.row_off + row] = 0;
     }
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        const float fn = M.relax(i, f[i], om, g, forced);
+    auto put = [&](int i, float fn) {
         const int lo = i == 0 ? 0 : ((i & 1) ? i : i - 1);
         const auto rd = buffer_of(fdst + (long long)lo * fst, (i == 0 ? 1 : 2) * fst * SB);
-        C::template store_buf<NT ? nt_store_policy<S>() : 0>(rd, (unsigned)((i - lo) * fst + pc) * SB, fn);
-    }
+        C::template store_buf<NT ? nt_store_policy<S>() : 0>(rd, (unsigned)pc * SB, (unsigned)((i - lo) * fst) * SB, fn);
+    };
+    // 2D: one straight path (the branch costs a small box 1 us a step in
+    // instruction fetches); 3D: the source is a branch of the whole wavefront
+    if (DIM == 2 || forced)
+        M.template relax<true>(f, om, g, put);
+    else
+        M.template relax<false>(f, om, g, put);
 
     if (band && D.force_mode == 0) {
         // interface band: keep U for the interpolation, hand back a clean F

@@ -71,12 +71,12 @@ struct Codec<ST_F32> {
         __builtin_nontemporal_store(v, p + i);
     }
     template <int AUX>
-    static __device__ __forceinline__ float load_buf(__amdgpu_buffer_rsrc_t r, unsigned off) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX));
+    static __device__ __forceinline__ float load_buf(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff = 0) {
+        return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, (int)soff, AUX));
     }
     template <int AUX>
-    static __device__ __forceinline__ void store_buf(__amdgpu_buffer_rsrc_t r, unsigned off, float v) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, 0, AUX);
+    static __device__ __forceinline__ void store_buf(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff, float v) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)off, (int)soff, AUX);
     }
     static __host__ __device__ __forceinline__ T from_double(double v) { return (float)v; }
     static __host__ __device__ __forceinline__ double to_double(T v) { return (double)v; }
@@ -94,12 +94,12 @@ struct Codec<ST_F16> {
         __builtin_nontemporal_store((_Float16)v, p + i);
     }
     template <int AUX>
-    static __device__ __forceinline__ float load_buf(__amdgpu_buffer_rsrc_t r, unsigned off) {
-        return (float)__builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, AUX));
+    static __device__ __forceinline__ float load_buf(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff = 0) {
+        return (float)__builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(r, (int)off, (int)soff, AUX));
     }
     template <int AUX>
-    static __device__ __forceinline__ void store_buf(__amdgpu_buffer_rsrc_t r, unsigned off, float v) {
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (_Float16)v), r, (int)off, 0,
+    static __device__ __forceinline__ void store_buf(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff, float v) {
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, (_Float16)v), r, (int)off, (int)soff,
                                               AUX);
     }
     // exchange values are narrowed through fp32 (nearest even at each step)
@@ -130,12 +130,12 @@ struct Codec<ST_BF16> {
         __builtin_nontemporal_store(f32_to_bf16_rne(v), p + i);
     }
     template <int AUX>
-    static __device__ __forceinline__ float load_buf(__amdgpu_buffer_rsrc_t r, unsigned off) {
-        return bf16_to_f32(__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, AUX));
+    static __device__ __forceinline__ float load_buf(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff = 0) {
+        return bf16_to_f32(__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, (int)soff, AUX));
     }
     template <int AUX>
-    static __device__ __forceinline__ void store_buf(__amdgpu_buffer_rsrc_t r, unsigned off, float v) {
-        __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16_rne(v), r, (int)off, 0, AUX);
+    static __device__ __forceinline__ void store_buf(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff, float v) {
+        __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16_rne(v), r, (int)off, (int)soff, AUX);
     }
     // exchange values are narrowed through fp32 (nearest even at each step)
     static __device__ __forceinline__ T from_double(double v) { return f32_to_bf16_rne((float)v); }
