@@ -64,13 +64,16 @@ int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 
 struct Layout {
     // byte offsets into the workspace
-    size_t drops, tiles_lb, tiles_all, f0, f1, F, Fq, U, Fout, rho, flags, pos0, pos1, phi, qdot, dropped,
+    size_t drops, tiles_lb, tiles_all, groups, blocks, part, f0, f1, F, Fq, U, Fout, rho, flags, pos0, pos1, phi, qdot, dropped,
         node_drop, tri, inc, inc_beg, inc_end, perm, chunks, status, partials, diag,
         xcnt0, xcnt1, xpos0, xpos1, tref, total;
     int nchunks;           // capacity of the 3D spreading chunk table
     long long cells;       // sum of cells
     long long flag_bytes;  // sum of band flags
     int ntot, ttot, max_tiles;
+    int nblocks = 0;       // interface chunks of all droplets (see k_diag_part)
+    int group_tiles = 1;   // tiles per group of the cell sums
+    int ngroups = 0;
     long long pop_elems;   // sum over droplets of Q * fst
     std::vector<long long> c_off, flag_off, f_off;
     std::vector<int> fst;
@@ -136,6 +139,9 @@ int tiles_of(const iblb_params& p, int shape) {
     return ceil_div(p.nx, bx) * ceil_div(p.ny, by) * (p.dim == 3 ? p.nz : 1);
 }
 
+// Chunks of kBlock nodes and 2 kBlock triangles of an interface.
+int iface_blocks(int nodes, int tris) { return std::max(ceil_div(nodes, kBlock), ceil_div(tris, 2 * kBlock)); }
+
 bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage, Layout& L,
           std::string& err) {
     if (n < 1) { err = "n_droplets must be >= 1"; return false; }
@@ -150,11 +156,13 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
     L.ntot = 0;
     L.ttot = 0;
     L.max_tiles = 0;
+    L.nblocks = 0;
     L.c_off.assign(n, 0);
     L.f_off.assign(n, 0);
     L.fst.assign(n, 0);
     L.pop_elems = 0;
     L.nchunks = 0;
+    L.ngroups = 0;
     L.flag_off.assign(n, 0);
     L.node_off.assign(n, 0);
     L.tri_off.assign(n, 0);
@@ -218,12 +226,16 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
         if (dim == 3) L.nchunks += nn[d];  // capacity: at worst one vertex per chunk
         L.tri_off[d] = L.ttot;
         L.ttot += T;
+        L.nblocks += iface_blocks(nn[d], T);
         L.row_off[d] = (int)L.rows;
         L.rows += (long long)p.ny * nz;
         if (L.rows >= (1LL << 31) / kCrossCap) { err = "too many lattice rows"; return false; }
         for (int s = 0; s < kShapes; ++s) tiles[s] += tiles_of(p, s);
     }
     for (int s = 0; s < kShapes; ++s) L.max_tiles = std::max(L.max_tiles, tiles[s]);
+    // a few thousand groups for a large box, single tiles for a small one
+    L.group_tiles = std::max(1, tiles[0] / 8192);
+    for (int d = 0; d < n; ++d) L.ngroups += ceil_div(tiles_of(P[d], 0), L.group_tiles);
     const long long C = L.cells;
     const int N = std::max(L.ntot, 1), T = std::max(L.ttot, 1);
     size_t o = 0;
@@ -231,6 +243,9 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
     L.drops = take(sizeof(DropDev) * n);
     L.tiles_lb = take(sizeof(int4) * L.max_tiles);
     L.tiles_all = take(sizeof(int4) * L.max_tiles);
+    L.groups = take(sizeof(int4) * L.ngroups);
+    L.blocks = take(sizeof(int4) * std::max(L.nblocks, 1));
+    L.part = take(sizeof(double) * P_SLOTS * std::max(L.nblocks, 1));
     L.f0 = take((size_t)L.pop_elems * sb);
     L.f1 = take((size_t)L.pop_elems * sb);
     L.F = take(sizeof(float) * dim * C);   // prescribed force fields
@@ -440,12 +455,19 @@ void push_tiles(const iblb_ctx* c, int d, int shape, std::vector<int4>& v) {
 }
 
 int rebuild_tiles(iblb_ctx* c) {
-    std::vector<int4> all, lb;
+    std::vector<int4> all, lb, groups, blocks;
     for (int d = 0; d < c->n; ++d) {
         // the list of all tiles (diagnostics) always has shape 0
-        c->drops[d].tile_off = (int)all.size();
+        DropDev& D = c->drops[d];
+        const int first = (int)all.size();
         push_tiles(c, d, 0, all);
-        c->drops[d].n_tiles = (int)all.size() - c->drops[d].tile_off;
+        D.grp_off = (int)groups.size();
+        for (int t = first; t < (int)all.size(); t += c->L.group_tiles)
+            groups.push_back(make_int4(d, t, std::min(c->L.group_tiles, (int)all.size() - t), 0));
+        D.n_grps = (int)groups.size() - D.grp_off;
+        D.blk_off = (int)blocks.size();
+        D.n_blks = iface_blocks(c->n_nodes[d], c->n_tris[d]);
+        for (int b = 0; b < D.n_blks; ++b) blocks.push_back(make_int4(d, b, 0, 0));
         if (c->drops[d].active) push_tiles(c, d, shape_of(c->variant), lb);
     }
     if (order_of(c->variant) == 0) {
@@ -459,6 +481,11 @@ int rebuild_tiles(iblb_ctx* c) {
     c->ntiles_lb = (int)lb.size();
     HIPCHK(c, hipMemcpyAsync(c->at<int4>(c->L.tiles_all), all.data(), sizeof(int4) * all.size(),
                              hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->at<int4>(c->L.groups), groups.data(), sizeof(int4) * groups.size(),
+                             hipMemcpyHostToDevice, c->stream));
+    if (!blocks.empty())
+        HIPCHK(c, hipMemcpyAsync(c->at<int4>(c->L.blocks), blocks.data(), sizeof(int4) * blocks.size(),
+                                 hipMemcpyHostToDevice, c->stream));
     if (!lb.empty())
         HIPCHK(c, hipMemcpyAsync(c->at<int4>(c->L.tiles_lb), lb.data(), sizeof(int4) * lb.size(),
                                  hipMemcpyHostToDevice, c->stream));
@@ -737,10 +764,10 @@ template <int DIM, int S>
 void launch_cell_sums(iblb_ctx* c) {
     using T = typename Codec<S>::T;
     const T* f = c->at<T>(c->cur ? c->L.f1 : c->L.f0);
-    const dim3 grid(c->ntiles_all), block(kBlock);
+    const dim3 grid(c->L.ngroups), block(kBlock);
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, grid, block, 0, c->stream, c->at<DropDev>(c->L.drops),
-                           c->at<int4>(c->L.tiles_all), f, c->at<float>(c->L.U), c->at<float>(c->L.rho),
+                           c->at<int4>(c->L.tiles_all), c->at<int4>(c->L.groups), f, c->at<float>(c->L.U), c->at<float>(c->L.rho),
                            c->at<float>(c->L.Fout), c->at<double>(c->L.partials));
     };
     go(k_cell_sums<DIM, S, 256>);  // tiles of shape 0
@@ -755,9 +782,33 @@ void launch_diag_d(iblb_ctx* c, bool cells = true) {
             default: launch_cell_sums<DIM, ST_BF16>(c); break;
         }
     }
-    hipLaunchKernelGGL(k_diag<DIM>, dim3(c->n), dim3(kBlock), 0, c->stream, c->at<DropDev>(c->L.drops),
-                       node_arrays(c, c->cur), cells ? (const double*)c->at<double>(c->L.partials) : nullptr,
+    const DropDev* D = c->at<DropDev>(c->L.drops);
+    const NodeArrays A = node_arrays(c, c->cur);
+    const int4* blocks = c->at<int4>(c->L.blocks);
+    double* part = c->at<double>(c->L.part);
+    if (c->L.nblocks > 0) {
+        const dim3 grid(c->L.nblocks), block(kBlock);
+        hipLaunchKernelGGL(k_diag_part<DIM>, grid, block, 0, c->stream, D, A, blocks, part);
+        if (DIM == 3)
+            hipLaunchKernelGGL(k_cross_dist, grid, block, 0, c->stream, D, A, blocks, (double)NAN, part);
+    }
+    hipLaunchKernelGGL(k_diag_final<DIM>, dim3(c->n), dim3(kFinalBlock), 0, c->stream, D,
+                       cells ? (const double*)c->at<double>(c->L.partials) : nullptr, (const double*)part,
                        c->at<DiagDev>(c->L.diag));
+}
+
+template <int DIM>
+void launch_contact(iblb_ctx* c, int d, double z_cut, double flat_tol, double* out) {
+    const DropDev* D = c->at<DropDev>(c->L.drops);
+    const NodeArrays A = node_arrays(c, c->cur);
+    // the droplet's own chunks; their partial results lie at its offset
+    const int4* blocks = c->at<int4>(c->L.blocks) + c->drops[d].blk_off;
+    double* part = c->at<double>(c->L.part);
+    const dim3 grid(c->drops[d].n_blks), block(kBlock);
+    hipLaunchKernelGGL(k_contact_height<DIM>, grid, block, 0, c->stream, D, A, blocks, part);
+    hipLaunchKernelGGL(k_contact_part<DIM>, grid, block, 0, c->stream, D, A, blocks, z_cut, flat_tol, part);
+    if (DIM == 3) hipLaunchKernelGGL(k_cross_dist, grid, block, 0, c->stream, D, A, blocks, z_cut, part);
+    hipLaunchKernelGGL(k_contact_final<DIM>, dim3(1), dim3(64), 0, c->stream, D, d, (const double*)part, out);
 }
 
 }  // namespace
@@ -1540,13 +1591,8 @@ int iblb_contact_radius(iblb_ctx* c, int d, double z_cut, double flat_tol, doubl
     if (!std::isfinite(z_cut) || !(flat_tol >= 0.0))
         return fail(c, IBLB_EINVAL, "z_cut must be finite and flat_tol >= 0");
     double* dev = c->at<double>(c->L.partials);
-    const NodeArrays A = node_arrays(c, c->cur);
-    if (c->dim == 2)
-        hipLaunchKernelGGL(k_contact<2>, dim3(1), dim3(kBlock), 0, c->stream, c->at<DropDev>(c->L.drops), d,
-                           A, z_cut, flat_tol, dev);
-    else
-        hipLaunchKernelGGL(k_contact<3>, dim3(1), dim3(kBlock), 0, c->stream, c->at<DropDev>(c->L.drops), d,
-                           A, z_cut, flat_tol, dev);
+    if (c->dim == 2) launch_contact<2>(c, d, z_cut, flat_tol, dev);
+    else launch_contact<3>(c, d, z_cut, flat_tol, dev);
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemcpyAsync(out, dev, 3 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));

@@ -21,8 +21,8 @@
 //                     the inside/outside classification of two viscosities
 //   k_inside_mask     that classification as a per-cell mask
 //   k_tri_ref         reference triangles of an elastic interface
-//   k_cell_sums,
-//   k_diag, k_contact FP64 reductions for the diagnostics and the contact
+//   k_cell_sums, k_diag_*, k_contact_*, k_cross_dist
+//                     FP64 reductions for the diagnostics and the contact
 //                     radius
 //
 // Populations are stored as deviations f_i - w_i (see lattice.hpp), in two
@@ -80,7 +80,8 @@ struct DropDev {
     int active;
     int node_off, n_nodes;
     int tri_off, n_tris;
-    int tile_off, n_tiles;  // this droplet's run in the list of all tiles
+    int grp_off, n_grps;  // this droplet's run in the list of tile groups (cell sums)
+    int blk_off, n_blks;  // and in the list of its interface's chunks (diagnostics)
     int wetting, n_exp, m_exp;
     int fst;              // element stride between population arrays (>= ppl nz)
     int ppl;              // elements per z-plane of a population array (>= nx ny):
@@ -1709,103 +1710,195 @@ __global__ void k_fill_f32(float* __restrict__ p, long long n, float v) {
 // ---------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
+#pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     return v;
 }
 template <typename T>
 __device__ __forceinline__ T wave_min(T v) {
+#pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
     return v;
 }
 template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
+#pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
     return v;
 }
 
-// Block-wide reduction of 256 threads (4 wavefronts); every thread gets the
-// result.  kind: 0 sum, 1 min, 2 max.
-__device__ double block_reduce(double v, int kind, double* sh) {
-    v = kind == 0 ? wave_sum(v) : (kind == 1 ? wave_min(v) : wave_max(v));
-    const int w = threadIdx.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[w] = v;
-    __syncthreads();
-    double r = sh[0];
-    for (int k = 1; k < kBlock / 64; ++k)
-        r = kind == 0 ? r + sh[k] : (kind == 1 ? fmin(r, sh[k]) : fmax(r, sh[k]));
-    return r;
-}
-
-// Per-tile partial sums over cells: [0] sum of f - w, [1..3] rho U,
-// [4..6] F of the last step.
+// Partial sums over the cells of a group of consecutive tiles of one droplet
+// (groups: droplet, first tile, tiles): [0] sum of f - w, [1..3] rho U,
+// [4..6] F of the last step.  HBM bound: the populations and fields are read
+// once.  The host makes the groups so large that a big box leaves a few
+// thousand partial sums, not one for every tile: k_diag_final reads them
+// with one workgroup per droplet (256x256x128: 32 768 tiles took most of a
+// millisecond there).
 template <int DIM, int S, int BX>
 __global__ __launch_bounds__(kBlock) void k_cell_sums(const DropDev* __restrict__ drops,
                                                       const int4* __restrict__ tiles,
+                                                      const int4* __restrict__ groups,
                                                       const typename Codec<S>::T* __restrict__ f_all,
                                                       const float* __restrict__ U_all,
                                                       const float* __restrict__ rho_all,
                                                       const float* __restrict__ Fout_all,
                                                       double* __restrict__ partials) {
-    __shared__ double sh[kBlock / 64];
+    __shared__ double sh[kBlock / 64][7];
     using L = Lattice<DIM>;
     constexpr int BY = kBlock / BX;
-    const int t = blockIdx.x;
-    const int4 tile = tiles[t];
-    const DropDev& D = drops[tile.x];
-    const int x = tile.y * BX + (int)(threadIdx.x % BX);
-    const int y = tile.z * BY + (int)(threadIdx.x / BX);
-    const int z = tile.w;
+    const int4 group = groups[blockIdx.x];
+    const DropDev& D = drops[group.x];
+    const int ncell = D.ncell;
+    const typename Codec<S>::T* __restrict__ f = f_all + D.f_off;
+    const float* __restrict__ U = U_all + (long long)DIM * D.c_off;
+    const float* __restrict__ Fo = Fout_all + (long long)DIM * D.c_off;
     double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (x < D.nx && y < D.ny) {
-        const int ncell = D.ncell;
-        const int cell = (z * D.ny + y) * D.nx + x;
-        const typename Codec<S>::T* f = f_all + D.f_off;
-        double s = 0.0;
-        const int pc = z * D.ppl + y * D.nx + x;
-        for (int i = 0; i < L::Q; ++i) s += (double)Codec<S>::load(f, i * D.fst + pc);
-        v[0] = s;
-        const double rho = rho_all[D.c_off + cell];
-        const float* U = U_all + (long long)DIM * D.c_off;
-        const float* Fo = Fout_all + (long long)DIM * D.c_off;
-        for (int a = 0; a < DIM; ++a) {
-            v[1 + a] = rho * (double)U[a * ncell + cell];
-            v[4 + a] = (double)Fo[a * ncell + cell];
+    for (int t = group.y; t < group.y + group.z; ++t) {
+        const int4 tile = tiles[t];
+        const int x = tile.y * BX + (int)(threadIdx.x % BX);
+        const int y = tile.z * BY + (int)(threadIdx.x / BX);
+        const int z = tile.w;
+        if (x < D.nx && y < D.ny) {
+            const int cell = (z * D.ny + y) * D.nx + x;
+            const int pc = z * D.ppl + y * D.nx + x;
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i < L::Q; ++i) s += (double)Codec<S>::load(f, i * D.fst + pc);
+            v[0] += s;
+            const float rho = rho_all[D.c_off + cell];
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) {
+                v[1 + a] += rho * (double)U[a * ncell + cell];
+                v[4 + a] += (double)Fo[a * ncell + cell];
+            }
         }
     }
+#pragma unroll
     for (int k = 0; k < 7; ++k) {
-        const double r = block_reduce(v[k], 0, sh);
-        if (threadIdx.x == 0) partials[(long long)t * 8 + k] = r;
+        const double w = wave_sum(v[k]);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][k] = w;
+    }
+    __syncthreads();
+    if (threadIdx.x < 7) {
+        const int k = threadIdx.x;
+        double r = sh[0][k];
+        for (int w = 1; w < kBlock / 64; ++w) r += sh[w][k];
+        partials[(long long)blockIdx.x * 8 + k] = r;
     }
 }
 
-// One block per droplet: cell partials + interface reductions.
-// partials may be null: interface quantities only (cell sums left zero).
-template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_diag(const DropDev* __restrict__ drops, NodeArrays A,
-                                                 const double* __restrict__ partials,
-                                                 DiagDev* __restrict__ out) {
-    __shared__ double sh[kBlock / 64];
-    const int d = blockIdx.x;
-    const DropDev& D = drops[d];
-    DiagDev r;
-    double acc[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (partials)
-        for (int t = D.tile_off + threadIdx.x; t < D.tile_off + D.n_tiles; t += kBlock)
-            for (int k = 0; k < 7; ++k) acc[k] += partials[(long long)t * 8 + k];
-    for (int k = 0; k < 7; ++k) acc[k] = block_reduce(acc[k], 0, sh);
-    r.mass_dev = acc[0];
-    for (int a = 0; a < 3; ++a) {
-        r.mom[a] = acc[1 + a];
-        r.sum_F[a] = acc[4 + a];
+// Interface reductions in two launches (three in 3D): workgroup b of
+// k_diag_part takes the chunk blocks[b] = (droplet, chunk) of kBlock nodes
+// and 2 kBlock triangles and leaves its partial results in part; one
+// workgroup per droplet joins them, in the order of the chunks, in
+// k_diag_final.  Bound by latency (scattered reads of a few MB): one
+// workgroup for a whole 20 252-vertex mesh took 1020 us, its chunks on 80
+// take 21 (and 20 to join them).
+enum PartSlot {
+    P_PHI = 0, P_DROP = 3, P_VOL = 6, P_AREA, P_HMIN, P_HMAX, P_UN, P_US, P_EMIN, P_EMAX, P_LO, P_HI,
+    P_CX, P_CY, P_CN, P_DIST, P_FLAT, P_SLOTS
+};
+// how the partial results of a slot are joined: 0 sum, 1 min, 2 max
+__device__ __forceinline__ int part_kind(int s) {
+    return s == P_HMIN || s == P_EMIN || s == P_LO ? 1 : (s == P_HMAX || s == P_UN || s == P_US || s == P_EMAX || s == P_HI ? 2 : 0);
+}
+__device__ __forceinline__ double part_none(int s) {
+    // of an empty interface: nothing below or above
+    return s == P_HMIN || s == P_EMIN || s == P_LO ? 1e300 : (s == P_HMAX || s == P_HI ? -1e300 : 0.0);
+}
+__device__ __forceinline__ double part_two(int kind, double a, double b) {
+    return kind == 0 ? a + b : (kind == 1 ? fmin(a, b) : fmax(a, b));
+}
+__device__ __forceinline__ double wave_join(int kind, double v) {
+    return kind == 0 ? wave_sum(v) : (kind == 1 ? wave_min(v) : wave_max(v));
+}
+// Partial results of slot s of droplet D's chunks, joined by this wavefront;
+// every lane gets the result.
+__device__ __forceinline__ double part_join(const DropDev& D, const double* __restrict__ part, int s) {
+    const int kind = part_kind(s);
+    double v = part_none(s);
+    for (int b = D.blk_off + (int)(threadIdx.x & 63); b < D.blk_off + D.n_blks; b += 64)
+        v = part_two(kind, v, part[(long long)b * P_SLOTS + s]);
+    return wave_join(kind, v);
+}
+// This workgroup's values of the slots first .. first + n - 1 joined over its
+// threads and left in part (chunk: the workgroup's (droplet, chunk) entry);
+// one barrier for all of them.
+template <int n>
+__device__ __forceinline__ void part_put(const DropDev& D, const int4& chunk, double* __restrict__ part, int first,
+                                         const double (&v)[n]) {
+    __shared__ double sh[kBlock / 64][n];
+#pragma unroll
+    for (int k = 0; k < n; ++k) {
+        const double w = wave_join(part_kind(first + k), v[k]);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6][k] = w;
     }
+    __syncthreads();
+    if ((int)threadIdx.x < n) {
+        const int k = threadIdx.x;
+        double r = sh[0][k];
+        for (int w = 1; w < kBlock / 64; ++w) r = part_two(part_kind(first + k), r, sh[w][k]);
+        part[(long long)(D.blk_off + chunk.y) * P_SLOTS + first + k] = r;
+    }
+}
 
+// Calls fn(P, v) for this thread's triangles (vertex positions, node ids) of
+// chunk k of droplet D.
+template <typename Fn>
+__device__ __forceinline__ void chunk_tris(const DropDev& D, const NodeArrays& A, int k, Fn&& fn) {
+    const int st = A.stride, ts = A.tstride;
+    for (int u = 0; u < 2; ++u) {
+        const int l = (2 * k + u) * kBlock + (int)threadIdx.x;
+        if (l >= D.n_tris) break;
+        const int t = D.tri_off + l;
+        const int v[3] = {A.tri[t], A.tri[ts + t], A.tri[2 * ts + t]};
+        double P[3][3];
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) P[m][a] = A.pos[a * st + v[m]];
+        fn(P, v);
+    }
+}
+
+// Calls fn(x, y) for the points where a triangle's edges, each taken by the
+// one of its two triangles that lists it in ascending order, cross the plane
+// at height zc.
+template <typename Fn>
+__device__ __forceinline__ void edge_crossings(const double P[3][3], const int v[3], double zc, Fn&& fn) {
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        const int m1 = m == 2 ? 0 : m + 1;
+        if (v[m] >= v[m1]) continue;
+        const double a0 = P[m][2] - zc, a1 = P[m1][2] - zc;
+        if (a0 * a1 < 0.0) {
+            const double s = a0 / (a0 - a1);
+            fn(P[m][0] + s * (P[m1][0] - P[m][0]), P[m][1] + s * (P[m1][1] - P[m][1]));
+        }
+    }
+}
+
+__device__ __forceinline__ double tri_area(const double P[3][3]) {
+    const double e1[3] = {P[1][0] - P[0][0], P[1][1] - P[0][1], P[1][2] - P[0][2]};
+    const double e2[3] = {P[2][0] - P[0][0], P[2][1] - P[0][1], P[2][2] - P[0][2]};
+    const double nt[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
+                          e1[0] * e2[1] - e1[1] * e2[0]};
+    return 0.5 * sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
+}
+
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_diag_part(const DropDev* __restrict__ drops, NodeArrays A,
+                                                      const int4* __restrict__ blocks,
+                                                      double* __restrict__ part) {
+    const int4 blk = blocks[blockIdx.x];
+    const DropDev& D = drops[blk.x];
     const int st = A.stride, N = D.n_nodes, j0 = D.node_off;
     double sphi[3] = {0, 0, 0}, sdrop[3] = {0, 0, 0};
     double vol = 0, area = 0, hmin = 1e300, hmax = -1e300, un = 0, us = 0;
     double emin = 1e300, emax = 0, lo = 1e300, hi = -1e300, cx = 0, cy = 0, cn = 0;
     const double zc = D.zcut;
-    for (int l = threadIdx.x; l < N; l += kBlock) {
+    const int l = blk.y * kBlock + (int)threadIdx.x;
+    if (l < N) {
         const int j = j0 + l;
         double q[3], fs[3], n[3], chi;
         if (DIM == 2) {
@@ -1815,206 +1908,206 @@ __global__ __launch_bounds__(kBlock) void k_diag(const DropDev* __restrict__ dro
         }
         double u2 = 0, udn = 0;
         for (int a = 0; a < DIM; ++a) {
-            sphi[a] += A.phi[a * st + j];
-            sdrop[a] += A.dropped[a * st + j];
+            sphi[a] = A.phi[a * st + j];
+            sdrop[a] = A.dropped[a * st + j];
             const double v = A.qdot[a * st + j];
             u2 += v * v;
             udn += v * n[a];
         }
-        un = fmax(un, fabs(udn));
-        us = fmax(us, sqrt(u2));
-        hmin = fmin(hmin, q[DIM - 1]);
-        hmax = fmax(hmax, q[DIM - 1]);
+        un = fabs(udn);
+        us = sqrt(u2);
+        hmin = hmax = q[DIM - 1];
         if (DIM == 2) {
             const int jp = j0 + (l == N - 1 ? 0 : l + 1);
             const double x0 = q[0], y0 = q[1], x1 = A.pos[jp], y1 = A.pos[st + jp];
-            vol += 0.5 * (x0 * y1 - x1 * y0);
+            vol = 0.5 * (x0 * y1 - x1 * y0);
             const double e = sqrt((x1 - x0) * (x1 - x0) + (y1 - y0) * (y1 - y0));
-            area += e;
-            emin = fmin(emin, e);
-            emax = fmax(emax, e);
+            area = e;
+            emin = emax = e;
             const double a0 = y0 - zc, a1 = y1 - zc;
-            if (a0 * a1 < 0.0 || (a0 == 0.0 && a1 != 0.0)) {
-                const double xs = x0 + a0 / (a0 - a1) * (x1 - x0);
-                lo = fmin(lo, xs);
-                hi = fmax(hi, xs);
-            }
+            if (a0 * a1 < 0.0 || (a0 == 0.0 && a1 != 0.0)) lo = hi = x0 + a0 / (a0 - a1) * (x1 - x0);
         }
     }
-    if (DIM == 3) {
-        const int ts = A.tstride;
-        for (int t = D.tri_off + threadIdx.x; t < D.tri_off + D.n_tris; t += kBlock) {
-            const int v[3] = {A.tri[t], A.tri[ts + t], A.tri[2 * ts + t]};
-            double P[3][3];
-            for (int m = 0; m < 3; ++m)
-                for (int a = 0; a < 3; ++a) P[m][a] = A.pos[a * st + v[m]];
+    if (DIM == 3)
+        chunk_tris(D, A, blk.y, [&](const double P[3][3], const int v[3]) {
             const double cr[3] = {P[1][1] * P[2][2] - P[1][2] * P[2][1],
                                   P[1][2] * P[2][0] - P[1][0] * P[2][2],
                                   P[1][0] * P[2][1] - P[1][1] * P[2][0]};
             vol += (P[0][0] * cr[0] + P[0][1] * cr[1] + P[0][2] * cr[2]) / 6.0;
-            const double e1[3] = {P[1][0] - P[0][0], P[1][1] - P[0][1], P[1][2] - P[0][2]};
-            const double e2[3] = {P[2][0] - P[0][0], P[2][1] - P[0][1], P[2][2] - P[0][2]};
-            const double nt[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
-                                  e1[0] * e2[1] - e1[1] * e2[0]};
-            area += 0.5 * sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
+            area += tri_area(P);
             for (int m = 0; m < 3; ++m) {
                 const int m1 = m == 2 ? 0 : m + 1;
-                const double dx = P[m1][0] - P[m][0], dy = P[m1][1] - P[m][1],
-                             dz = P[m1][2] - P[m][2];
+                const double dx = P[m1][0] - P[m][0], dy = P[m1][1] - P[m][1], dz = P[m1][2] - P[m][2];
                 const double e = sqrt(dx * dx + dy * dy + dz * dz);
                 emin = fmin(emin, e);
                 emax = fmax(emax, e);
-                if (v[m] < v[m1]) {  // each edge once
-                    const double a0 = P[m][2] - zc, a1 = P[m1][2] - zc;
-                    if (a0 * a1 < 0.0) {
-                        const double s = a0 / (a0 - a1);
-                        cx += P[m][0] + s * dx;
-                        cy += P[m][1] + s * dy;
-                        cn += 1.0;
-                    }
-                }
             }
-        }
-    }
-    for (int a = 0; a < 3; ++a) {
-        r.sum_phi[a] = block_reduce(sphi[a], 0, sh);
-        r.dropped[a] = block_reduce(sdrop[a], 0, sh);
-    }
-    r.volume = block_reduce(vol, 0, sh);
-    r.area = block_reduce(area, 0, sh);
-    r.min_h = block_reduce(hmin, 1, sh);
-    r.max_h = block_reduce(hmax, 2, sh);
-    r.max_un = block_reduce(un, 2, sh);
-    r.max_u = block_reduce(us, 2, sh);
-    r.edge_min = block_reduce(emin, 1, sh);
-    r.edge_max = block_reduce(emax, 2, sh);
-    r.cross_lo = block_reduce(lo, 1, sh);
-    r.cross_hi = block_reduce(hi, 2, sh);
-    r.cross_r = 0.0;
-    r.cross_n = 0.0;
-    if (DIM == 3) {
-        const double n = block_reduce(cn, 0, sh);
-        const double mx = block_reduce(cx, 0, sh) / n, my = block_reduce(cy, 0, sh) / n;
-        double dsum = 0.0;
-        const int ts = A.tstride;
-        for (int t = D.tri_off + threadIdx.x; t < D.tri_off + D.n_tris; t += kBlock) {
-            const int v[3] = {A.tri[t], A.tri[ts + t], A.tri[2 * ts + t]};
-            for (int m = 0; m < 3; ++m) {
-                const int m1 = m == 2 ? 0 : m + 1;
-                if (v[m] >= v[m1]) continue;
-                const double z0 = A.pos[2 * st + v[m]] - zc, z1 = A.pos[2 * st + v[m1]] - zc;
-                if (z0 * z1 < 0.0) {
-                    const double s = z0 / (z0 - z1);
-                    const double px = A.pos[v[m]] + s * (A.pos[v[m1]] - A.pos[v[m]]);
-                    const double py = A.pos[st + v[m]] + s * (A.pos[st + v[m1]] - A.pos[st + v[m]]);
-                    dsum += sqrt((px - mx) * (px - mx) + (py - my) * (py - my));
-                }
-            }
-        }
-        r.cross_r = block_reduce(dsum, 0, sh) / n;
-        r.cross_n = n;
-    }
-    if (threadIdx.x == 0) out[d] = r;
+            edge_crossings(P, v, zc, [&](double x, double y) {
+                cx += x;
+                cy += y;
+                cn += 1.0;
+            });
+        });
+    const double v[P_DIST] = {sphi[0], sphi[1], sphi[2], sdrop[0], sdrop[1], sdrop[2], vol, area, hmin, hmax,
+                              un, us, emin, emax, lo, hi, cx, cy, cn};
+    part_put(D, blk, part, 0, v);
 }
 
-// Contact radius of droplet d at the positions A.pos by the two protocols
-// of Sec. Dynamics, one workgroup.  (i) the interface cut by the plane
-// (2D: line) at height zcut: 2D half the distance between the outermost
-// crossings, 3D the mean distance of the edge crossings to their centre.
-// (ii) the flat lower region: the elements (2D edges, 3D triangles) whose
-// nodes all lie below the mid-height between the lowest and the highest
-// node and differ in height by less than tol; 2D half its length, 3D the
-// radius of the disc of its area.  out: r_i (NaN without crossings), r_ii,
-// number of crossings.
+// 3D: sum of the crossings' distances from their centre, which every chunk
+// forms from all chunks' partial results.  zcut: height of the plane (NaN:
+// the droplet's own).
+__global__ __launch_bounds__(kBlock) void k_cross_dist(const DropDev* __restrict__ drops, NodeArrays A,
+                                                       const int4* __restrict__ blocks, double zcut,
+                                                       double* __restrict__ part) {
+    const int4 blk = blocks[blockIdx.x];
+    const DropDev& D = drops[blk.x];
+    const double n = part_join(D, part, P_CN);
+    const double mx = part_join(D, part, P_CX) / n, my = part_join(D, part, P_CY) / n;
+    double d = 0.0;
+    chunk_tris(D, A, blk.y, [&](const double P[3][3], const int v[3]) {
+        edge_crossings(P, v, zcut == zcut ? zcut : D.zcut, [&](double x, double y) {
+            d += sqrt((x - mx) * (x - mx) + (y - my) * (y - my));
+        });
+    });
+    const double v[1] = {d};
+    part_put(D, blk, part, P_DIST, v);
+}
+
+// One workgroup per droplet: cell partials + interface partials joined.
+// partials may be null: interface quantities only (cell sums left zero).
+constexpr int kFinalBlock = 1024;
 template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_contact(const DropDev* __restrict__ drops, int d, NodeArrays A,
-                                                    double zcut, double tol, double* __restrict__ out) {
-    __shared__ double sh[kBlock / 64];
+__global__ __launch_bounds__(kFinalBlock) void k_diag_final(const DropDev* __restrict__ drops,
+                                                            const double* __restrict__ partials,
+                                                            const double* __restrict__ part,
+                                                            DiagDev* __restrict__ out) {
+    constexpr int W = kFinalBlock / 64;
+    __shared__ double cells[W][7];
+    __shared__ double joined[P_SLOTS];
+    const int d = blockIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const DropDev& D = drops[d];
-    const int st = A.stride, N = D.n_nodes, j0 = D.node_off, H = DIM - 1;
-    double hmin = 1e300, hmax = -1e300;
-    for (int l = threadIdx.x; l < N; l += kBlock) {
-        const double h = A.pos[H * st + j0 + l];
-        hmin = fmin(hmin, h);
-        hmax = fmax(hmax, h);
+    double acc[7] = {0, 0, 0, 0, 0, 0, 0};
+    if (partials)
+        for (int t = D.grp_off + threadIdx.x; t < D.grp_off + D.n_grps; t += kFinalBlock)
+#pragma unroll
+            for (int k = 0; k < 7; ++k) acc[k] += partials[(long long)t * 8 + k];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        acc[k] = wave_sum(acc[k]);
+        if (lane == 0) cells[w][k] = acc[k];
     }
-    hmin = block_reduce(hmin, 1, sh);
-    hmax = block_reduce(hmax, 2, sh);
+    for (int s = w; s < P_FLAT; s += W) {
+        // the crossings' slots are written in 3D only
+        const double v = DIM == 3 || s < P_CX ? part_join(D, part, s) : 0.0;
+        if (lane == 0) joined[s] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    DiagDev r;
+    for (int k = 0; k < 7; ++k) {
+        acc[k] = cells[0][k];
+        for (int u = 1; u < W; ++u) acc[k] += cells[u][k];
+    }
+    r.mass_dev = acc[0];
+    for (int a = 0; a < 3; ++a) {
+        r.mom[a] = acc[1 + a];
+        r.sum_F[a] = acc[4 + a];
+        r.sum_phi[a] = joined[P_PHI + a];
+        r.dropped[a] = joined[P_DROP + a];
+    }
+    r.volume = joined[P_VOL];
+    r.area = joined[P_AREA];
+    r.min_h = joined[P_HMIN];
+    r.max_h = joined[P_HMAX];
+    r.max_un = joined[P_UN];
+    r.max_u = joined[P_US];
+    r.edge_min = joined[P_EMIN];
+    r.edge_max = joined[P_EMAX];
+    r.cross_lo = joined[P_LO];
+    r.cross_hi = joined[P_HI];
+    r.cross_n = joined[P_CN];
+    r.cross_r = DIM == 3 ? joined[P_DIST] / joined[P_CN] : 0.0;
+    out[d] = r;
+}
+
+// Contact radius of one droplet at the positions A.pos by the two protocols
+// of Sec. Dynamics.  (i) the interface cut by the plane (2D: line) at height
+// zcut: 2D half the distance between the outermost crossings, 3D the mean
+// distance of the edge crossings to their centre.  (ii) the flat lower
+// region: the elements (2D edges, 3D triangles) whose nodes all lie below
+// the mid-height between the lowest and the highest node and differ in
+// height by less than tol; 2D half its length, 3D the radius of the disc of
+// its area.  Chunks of the droplet (see k_diag_part) on one workgroup each:
+// k_contact_height, k_contact_part, in 3D k_cross_dist, then
+// k_contact_final, which writes r_i (NaN without crossings), r_ii and the
+// number of crossings to out (20 252 vertices: 219 us on one workgroup, about 25
+// so).
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_contact_height(const DropDev* __restrict__ drops, NodeArrays A,
+                                                           const int4* __restrict__ blocks,
+                                                           double* __restrict__ part) {
+    const int4 blk = blocks[blockIdx.x];
+    const DropDev& D = drops[blk.x];
+    const int l = blk.y * kBlock + (int)threadIdx.x;
+    double hmin = 1e300, hmax = -1e300;
+    if (l < D.n_nodes) hmin = hmax = A.pos[(DIM - 1) * A.stride + D.node_off + l];
+    const double v[2] = {hmin, hmax};
+    part_put(D, blk, part, P_HMIN, v);
+}
+
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_contact_part(const DropDev* __restrict__ drops, NodeArrays A,
+                                                         const int4* __restrict__ blocks, double zcut, double tol,
+                                                         double* __restrict__ part) {
+    const int4 blk = blocks[blockIdx.x];
+    const DropDev& D = drops[blk.x];
+    const int st = A.stride, N = D.n_nodes, j0 = D.node_off;
+    const double hmin = part_join(D, part, P_HMIN), hmax = part_join(D, part, P_HMAX);
     const double mid = 0.5 * (hmin + hmax);
     double lo = 1e300, hi = -1e300, cx = 0.0, cy = 0.0, cn = 0.0, flat = 0.0;
-    const int ts = A.tstride;
     if (DIM == 2) {
-        for (int l = threadIdx.x; l < N; l += kBlock) {
+        const int l = blk.y * kBlock + (int)threadIdx.x;
+        if (l < N) {
             const int j = j0 + l, jp = j0 + (l == N - 1 ? 0 : l + 1);
             const double x0 = A.pos[j], y0 = A.pos[st + j], x1 = A.pos[jp], y1 = A.pos[st + jp];
             const double a0 = y0 - zcut, a1 = y1 - zcut;
             if (a0 * a1 < 0.0 || (a0 == 0.0 && a1 != 0.0)) {
-                const double xs = x0 + a0 / (a0 - a1) * (x1 - x0);
-                lo = fmin(lo, xs);
-                hi = fmax(hi, xs);
-                cn += 1.0;
+                lo = hi = x0 + a0 / (a0 - a1) * (x1 - x0);
+                cn = 1.0;
             }
             if (y0 < mid && y1 < mid && fabs(y1 - y0) < tol)
-                flat += sqrt((x1 - x0) * (x1 - x0) + (y1 - y0) * (y1 - y0));
+                flat = sqrt((x1 - x0) * (x1 - x0) + (y1 - y0) * (y1 - y0));
         }
     } else {
-        for (int t = D.tri_off + threadIdx.x; t < D.tri_off + D.n_tris; t += kBlock) {
-            const int v[3] = {A.tri[t], A.tri[ts + t], A.tri[2 * ts + t]};
-            double P[3][3];
-            for (int m = 0; m < 3; ++m)
-                for (int a = 0; a < 3; ++a) P[m][a] = A.pos[a * st + v[m]];
-            for (int m = 0; m < 3; ++m) {
-                const int m1 = m == 2 ? 0 : m + 1;
-                if (v[m] >= v[m1]) continue;  // each edge once
-                const double a0 = P[m][2] - zcut, a1 = P[m1][2] - zcut;
-                if (a0 * a1 < 0.0) {
-                    const double s = a0 / (a0 - a1);
-                    cx += P[m][0] + s * (P[m1][0] - P[m][0]);
-                    cy += P[m][1] + s * (P[m1][1] - P[m][1]);
-                    cn += 1.0;
-                }
-            }
+        chunk_tris(D, A, blk.y, [&](const double P[3][3], const int v[3]) {
+            edge_crossings(P, v, zcut, [&](double x, double y) {
+                cx += x;
+                cy += y;
+                cn += 1.0;
+            });
             const double zlo = fmin(fmin(P[0][2], P[1][2]), P[2][2]);
             const double zhi = fmax(fmax(P[0][2], P[1][2]), P[2][2]);
-            if (zhi < mid && zhi - zlo < tol) {
-                const double e1[3] = {P[1][0] - P[0][0], P[1][1] - P[0][1], P[1][2] - P[0][2]};
-                const double e2[3] = {P[2][0] - P[0][0], P[2][1] - P[0][1], P[2][2] - P[0][2]};
-                const double nt[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2],
-                                      e1[0] * e2[1] - e1[1] * e2[0]};
-                flat += 0.5 * sqrt(nt[0] * nt[0] + nt[1] * nt[1] + nt[2] * nt[2]);
-            }
-        }
+            if (zhi < mid && zhi - zlo < tol) flat += tri_area(P);
+        });
     }
-    lo = block_reduce(lo, 1, sh);
-    hi = block_reduce(hi, 2, sh);
-    cn = block_reduce(cn, 0, sh);
-    flat = block_reduce(flat, 0, sh);
+    const double c[5] = {lo, hi, cx, cy, cn}, g[1] = {flat};
+    part_put(D, blk, part, P_LO, c);
+    part_put(D, blk, part, P_FLAT, g);
+}
+
+// One wavefront.
+template <int DIM>
+__global__ __launch_bounds__(64) void k_contact_final(const DropDev* __restrict__ drops, int d,
+                                                      const double* __restrict__ part, double* __restrict__ out) {
+    const DropDev& D = drops[d];
+    const double cn = part_join(D, part, P_CN), flat = part_join(D, part, P_FLAT);
     double ri = __builtin_nan("");
     if (DIM == 2) {
+        const double lo = part_join(D, part, P_LO), hi = part_join(D, part, P_HI);
         if (cn >= 2.0) ri = 0.5 * (hi - lo);
     } else {
-        cx = block_reduce(cx, 0, sh);
-        cy = block_reduce(cy, 0, sh);
-        double dsum = 0.0;
-        if (cn > 0.0) {
-            const double mx = cx / cn, my = cy / cn;
-            for (int t = D.tri_off + threadIdx.x; t < D.tri_off + D.n_tris; t += kBlock) {
-                const int v[3] = {A.tri[t], A.tri[ts + t], A.tri[2 * ts + t]};
-                for (int m = 0; m < 3; ++m) {
-                    const int m1 = m == 2 ? 0 : m + 1;
-                    if (v[m] >= v[m1]) continue;
-                    const double z0 = A.pos[2 * st + v[m]] - zcut, z1 = A.pos[2 * st + v[m1]] - zcut;
-                    if (z0 * z1 < 0.0) {
-                        const double s = z0 / (z0 - z1);
-                        const double px = A.pos[v[m]] + s * (A.pos[v[m1]] - A.pos[v[m]]);
-                        const double py = A.pos[st + v[m]] + s * (A.pos[st + v[m1]] - A.pos[st + v[m]]);
-                        dsum += sqrt((px - mx) * (px - mx) + (py - my) * (py - my));
-                    }
-                }
-            }
-        }
-        dsum = block_reduce(dsum, 0, sh);
-        if (cn > 0.0) ri = dsum / cn;
+        const double dist = part_join(D, part, P_DIST);
+        if (cn > 0.0) ri = dist / cn;
     }
     if (threadIdx.x == 0) {
         out[0] = ri;
