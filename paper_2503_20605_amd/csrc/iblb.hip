@@ -72,6 +72,7 @@ struct Layout {
     long long flag_bytes;  // sum of band flags
     int ntot, ttot, max_tiles;
     int nblocks = 0;       // interface chunks of all droplets (see k_diag_part)
+    int most_blocks = 0;   // of one droplet
     int group_tiles = 1;   // tiles per group of the cell sums
     int ngroups = 0;
     long long pop_elems;   // sum over droplets of Q * fst
@@ -157,6 +158,7 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
     L.ttot = 0;
     L.max_tiles = 0;
     L.nblocks = 0;
+    L.most_blocks = 0;
     L.c_off.assign(n, 0);
     L.f_off.assign(n, 0);
     L.fst.assign(n, 0);
@@ -227,6 +229,7 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
         L.tri_off[d] = L.ttot;
         L.ttot += T;
         L.nblocks += iface_blocks(nn[d], T);
+        L.most_blocks = std::max(L.most_blocks, iface_blocks(nn[d], T));
         L.row_off[d] = (int)L.rows;
         L.rows += (long long)p.ny * nz;
         if (L.rows >= (1LL << 31) / kCrossCap) { err = "too many lattice rows"; return false; }
@@ -242,9 +245,10 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
     L.drops = take(sizeof(DropDev) * n);
     L.tiles_lb = take(sizeof(int4) * L.max_tiles);
-    L.tiles_all = take(sizeof(int4) * L.max_tiles);
-    L.groups = take(sizeof(int4) * L.ngroups);
-    L.blocks = take(sizeof(int4) * std::max(L.nblocks, 1));
+    // all tiles, their groups and the interfaces' chunks: one list, uploaded at once
+    L.tiles_all = take(sizeof(int4) * ((size_t)tiles[0] + L.ngroups + L.nblocks));
+    L.groups = L.tiles_all + sizeof(int4) * tiles[0];
+    L.blocks = L.groups + sizeof(int4) * L.ngroups;
     L.part = take(sizeof(double) * P_SLOTS * std::max(L.nblocks, 1));
     L.f0 = take((size_t)L.pop_elems * sb);
     L.f1 = take((size_t)L.pop_elems * sb);
@@ -292,7 +296,7 @@ struct iblb_ctx {
     int cur = 0;  // buffer holding the current post-collision populations
     bool any_visc = false;  // some droplet has two viscosities
     int variant = 0;  // lattice-kernel variant; its tile shape is shape_of(variant)
-    int ntiles_lb = 0, ntiles_all = 0;
+    int ntiles_lb = 0;
     bool tiles_dirty = true;
     std::vector<int4> tiles_h;
     int graph_steps = 64;
@@ -477,15 +481,11 @@ int rebuild_tiles(iblb_ctx* c) {
         for (size_t b = 0; b < lb.size(); ++b) runs[b] = lb[xcd_run_tile((int)b, (int)lb.size())];
         lb.swap(runs);
     }
-    c->ntiles_all = (int)all.size();
+    all.insert(all.end(), groups.begin(), groups.end());
+    all.insert(all.end(), blocks.begin(), blocks.end());
     c->ntiles_lb = (int)lb.size();
     HIPCHK(c, hipMemcpyAsync(c->at<int4>(c->L.tiles_all), all.data(), sizeof(int4) * all.size(),
                              hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->at<int4>(c->L.groups), groups.data(), sizeof(int4) * groups.size(),
-                             hipMemcpyHostToDevice, c->stream));
-    if (!blocks.empty())
-        HIPCHK(c, hipMemcpyAsync(c->at<int4>(c->L.blocks), blocks.data(), sizeof(int4) * blocks.size(),
-                                 hipMemcpyHostToDevice, c->stream));
     if (!lb.empty())
         HIPCHK(c, hipMemcpyAsync(c->at<int4>(c->L.tiles_lb), lb.data(), sizeof(int4) * lb.size(),
                                  hipMemcpyHostToDevice, c->stream));
@@ -786,6 +786,12 @@ void launch_diag_d(iblb_ctx* c, bool cells = true) {
     const NodeArrays A = node_arrays(c, c->cur);
     const int4* blocks = c->at<int4>(c->L.blocks);
     double* part = c->at<double>(c->L.part);
+    const double* sums = cells ? (const double*)c->at<double>(c->L.partials) : nullptr;
+    if (c->L.most_blocks <= kFewBlocks) {
+        hipLaunchKernelGGL(k_diag_one<DIM>, dim3(c->n), dim3(kBlock), 0, c->stream, D, A, sums,
+                           c->at<DiagDev>(c->L.diag));
+        return;
+    }
     if (c->L.nblocks > 0) {
         const dim3 grid(c->L.nblocks), block(kBlock);
         hipLaunchKernelGGL(k_diag_part<DIM>, grid, block, 0, c->stream, D, A, blocks, part);
@@ -793,8 +799,7 @@ void launch_diag_d(iblb_ctx* c, bool cells = true) {
             hipLaunchKernelGGL(k_cross_dist, grid, block, 0, c->stream, D, A, blocks, (double)NAN, part);
     }
     hipLaunchKernelGGL(k_diag_final<DIM>, dim3(c->n), dim3(kFinalBlock), 0, c->stream, D,
-                       cells ? (const double*)c->at<double>(c->L.partials) : nullptr, (const double*)part,
-                       c->at<DiagDev>(c->L.diag));
+                       sums, part, c->at<DiagDev>(c->L.diag));
 }
 
 template <int DIM>
@@ -805,10 +810,14 @@ void launch_contact(iblb_ctx* c, int d, double z_cut, double flat_tol, double* o
     const int4* blocks = c->at<int4>(c->L.blocks) + c->drops[d].blk_off;
     double* part = c->at<double>(c->L.part);
     const dim3 grid(c->drops[d].n_blks), block(kBlock);
+    if (c->drops[d].n_blks <= kFewBlocks) {
+        hipLaunchKernelGGL(k_contact_one<DIM>, dim3(1), block, 0, c->stream, D, d, A, z_cut, flat_tol, out);
+        return;
+    }
     hipLaunchKernelGGL(k_contact_height<DIM>, grid, block, 0, c->stream, D, A, blocks, part);
     hipLaunchKernelGGL(k_contact_part<DIM>, grid, block, 0, c->stream, D, A, blocks, z_cut, flat_tol, part);
     if (DIM == 3) hipLaunchKernelGGL(k_cross_dist, grid, block, 0, c->stream, D, A, blocks, z_cut, part);
-    hipLaunchKernelGGL(k_contact_final<DIM>, dim3(1), dim3(64), 0, c->stream, D, d, (const double*)part, out);
+    hipLaunchKernelGGL(k_contact_final<DIM>, dim3(1), dim3(64), 0, c->stream, D, d, part, out);
 }
 
 }  // namespace

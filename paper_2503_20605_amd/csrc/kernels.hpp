@@ -1787,13 +1787,16 @@ __global__ __launch_bounds__(kBlock) void k_cell_sums(const DropDev* __restrict_
     }
 }
 
-// Interface reductions in two launches (three in 3D): workgroup b of
-// k_diag_part takes the chunk blocks[b] = (droplet, chunk) of kBlock nodes
-// and 2 kBlock triangles and leaves its partial results in part; one
-// workgroup per droplet joins them, in the order of the chunks, in
-// k_diag_final.  Bound by latency (scattered reads of a few MB): one
-// workgroup for a whole 20 252-vertex mesh took 1020 us, its chunks on 80
-// take 21 (and 20 to join them).
+// Interface reductions in two launches (three in 3D): each workgroup of
+// k_diag_part takes one chunk (droplet, chunk) of kBlock nodes and 2 kBlock
+// triangles and leaves its partial results in part; one workgroup per droplet
+// joins them, in the order of the chunks, in k_diag_final.  Bound by latency
+// (scattered reads of a few MB): one workgroup for a whole 20 252-vertex mesh
+// took 1020 us, its chunks on 80 take 20 and 16 to join them.
+struct Chunk {
+    int c, n;      // this workgroup's chunk of n
+    double* part;  // partial results of the droplet's chunks
+};
 enum PartSlot {
     P_PHI = 0, P_DROP = 3, P_VOL = 6, P_AREA, P_HMIN, P_HMAX, P_UN, P_US, P_EMIN, P_EMAX, P_LO, P_HI,
     P_CX, P_CY, P_CN, P_DIST, P_FLAT, P_SLOTS
@@ -1812,21 +1815,20 @@ __device__ __forceinline__ double part_two(int kind, double a, double b) {
 __device__ __forceinline__ double wave_join(int kind, double v) {
     return kind == 0 ? wave_sum(v) : (kind == 1 ? wave_min(v) : wave_max(v));
 }
-// Partial results of slot s of droplet D's chunks, joined by this wavefront;
-// every lane gets the result.
-__device__ __forceinline__ double part_join(const DropDev& D, const double* __restrict__ part, int s) {
+// Partial results of slot s of the chunks, joined by this wavefront; every
+// lane gets the result.
+__device__ __forceinline__ double part_join(const Chunk& ch, int s) {
+    if (ch.n == 1) return ch.part[s];
     const int kind = part_kind(s);
     double v = part_none(s);
-    for (int b = D.blk_off + (int)(threadIdx.x & 63); b < D.blk_off + D.n_blks; b += 64)
-        v = part_two(kind, v, part[(long long)b * P_SLOTS + s]);
+    for (int b = (int)(threadIdx.x & 63); b < ch.n; b += 64) v = part_two(kind, v, ch.part[(long long)b * P_SLOTS + s]);
     return wave_join(kind, v);
 }
 // This workgroup's values of the slots first .. first + n - 1 joined over its
 // threads and left in part (chunk: the workgroup's (droplet, chunk) entry);
 // one barrier for all of them.
 template <int n>
-__device__ __forceinline__ void part_put(const DropDev& D, const int4& chunk, double* __restrict__ part, int first,
-                                         const double (&v)[n]) {
+__device__ __forceinline__ void part_put(const Chunk& ch, int first, const double (&v)[n]) {
     __shared__ double sh[kBlock / 64][n];
 #pragma unroll
     for (int k = 0; k < n; ++k) {
@@ -1838,18 +1840,15 @@ __device__ __forceinline__ void part_put(const DropDev& D, const int4& chunk, do
         const int k = threadIdx.x;
         double r = sh[0][k];
         for (int w = 1; w < kBlock / 64; ++w) r = part_two(part_kind(first + k), r, sh[w][k]);
-        part[(long long)(D.blk_off + chunk.y) * P_SLOTS + first + k] = r;
+        ch.part[(long long)ch.c * P_SLOTS + first + k] = r;
     }
 }
 
-// Calls fn(P, v) for this thread's triangles (vertex positions, node ids) of
-// chunk k of droplet D.
+// Calls fn(P, v) for this thread's triangles (vertex positions, node ids).
 template <typename Fn>
-__device__ __forceinline__ void chunk_tris(const DropDev& D, const NodeArrays& A, int k, Fn&& fn) {
+__device__ __forceinline__ void chunk_tris(const DropDev& D, const NodeArrays& A, const Chunk& ch, Fn&& fn) {
     const int st = A.stride, ts = A.tstride;
-    for (int u = 0; u < 2; ++u) {
-        const int l = (2 * k + u) * kBlock + (int)threadIdx.x;
-        if (l >= D.n_tris) break;
+    for (int l = ch.c * kBlock + (int)threadIdx.x; l < D.n_tris; l += ch.n * kBlock) {
         const int t = D.tri_off + l;
         const int v[3] = {A.tri[t], A.tri[ts + t], A.tri[2 * ts + t]};
         double P[3][3];
@@ -1887,18 +1886,13 @@ __device__ __forceinline__ double tri_area(const double P[3][3]) {
 }
 
 template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_diag_part(const DropDev* __restrict__ drops, NodeArrays A,
-                                                      const int4* __restrict__ blocks,
-                                                      double* __restrict__ part) {
-    const int4 blk = blocks[blockIdx.x];
-    const DropDev& D = drops[blk.x];
+__device__ __forceinline__ void diag_part(const DropDev& D, const NodeArrays& A, const Chunk& ch) {
     const int st = A.stride, N = D.n_nodes, j0 = D.node_off;
     double sphi[3] = {0, 0, 0}, sdrop[3] = {0, 0, 0};
     double vol = 0, area = 0, hmin = 1e300, hmax = -1e300, un = 0, us = 0;
     double emin = 1e300, emax = 0, lo = 1e300, hi = -1e300, cx = 0, cy = 0, cn = 0;
     const double zc = D.zcut;
-    const int l = blk.y * kBlock + (int)threadIdx.x;
-    if (l < N) {
+    for (int l = ch.c * kBlock + (int)threadIdx.x; l < N; l += ch.n * kBlock) {
         const int j = j0 + l;
         double q[3], fs[3], n[3], chi;
         if (DIM == 2) {
@@ -1908,28 +1902,34 @@ __global__ __launch_bounds__(kBlock) void k_diag_part(const DropDev* __restrict_
         }
         double u2 = 0, udn = 0;
         for (int a = 0; a < DIM; ++a) {
-            sphi[a] = A.phi[a * st + j];
-            sdrop[a] = A.dropped[a * st + j];
+            sphi[a] += A.phi[a * st + j];
+            sdrop[a] += A.dropped[a * st + j];
             const double v = A.qdot[a * st + j];
             u2 += v * v;
             udn += v * n[a];
         }
-        un = fabs(udn);
-        us = sqrt(u2);
-        hmin = hmax = q[DIM - 1];
+        un = fmax(un, fabs(udn));
+        us = fmax(us, sqrt(u2));
+        hmin = fmin(hmin, q[DIM - 1]);
+        hmax = fmax(hmax, q[DIM - 1]);
         if (DIM == 2) {
             const int jp = j0 + (l == N - 1 ? 0 : l + 1);
             const double x0 = q[0], y0 = q[1], x1 = A.pos[jp], y1 = A.pos[st + jp];
-            vol = 0.5 * (x0 * y1 - x1 * y0);
+            vol += 0.5 * (x0 * y1 - x1 * y0);
             const double e = sqrt((x1 - x0) * (x1 - x0) + (y1 - y0) * (y1 - y0));
-            area = e;
-            emin = emax = e;
+            area += e;
+            emin = fmin(emin, e);
+            emax = fmax(emax, e);
             const double a0 = y0 - zc, a1 = y1 - zc;
-            if (a0 * a1 < 0.0 || (a0 == 0.0 && a1 != 0.0)) lo = hi = x0 + a0 / (a0 - a1) * (x1 - x0);
+            if (a0 * a1 < 0.0 || (a0 == 0.0 && a1 != 0.0)) {
+                const double xs = x0 + a0 / (a0 - a1) * (x1 - x0);
+                lo = fmin(lo, xs);
+                hi = fmax(hi, xs);
+            }
         }
     }
     if (DIM == 3)
-        chunk_tris(D, A, blk.y, [&](const double P[3][3], const int v[3]) {
+        chunk_tris(D, A, ch, [&](const double P[3][3], const int v[3]) {
             const double cr[3] = {P[1][1] * P[2][2] - P[1][2] * P[2][1],
                                   P[1][2] * P[2][0] - P[1][0] * P[2][2],
                                   P[1][0] * P[2][1] - P[1][1] * P[2][0]};
@@ -1950,45 +1950,38 @@ __global__ __launch_bounds__(kBlock) void k_diag_part(const DropDev* __restrict_
         });
     const double v[P_DIST] = {sphi[0], sphi[1], sphi[2], sdrop[0], sdrop[1], sdrop[2], vol, area, hmin, hmax,
                               un, us, emin, emax, lo, hi, cx, cy, cn};
-    part_put(D, blk, part, 0, v);
+    part_put(ch, 0, v);
 }
 
 // 3D: sum of the crossings' distances from their centre, which every chunk
 // forms from all chunks' partial results.  zcut: height of the plane (NaN:
 // the droplet's own).
-__global__ __launch_bounds__(kBlock) void k_cross_dist(const DropDev* __restrict__ drops, NodeArrays A,
-                                                       const int4* __restrict__ blocks, double zcut,
-                                                       double* __restrict__ part) {
-    const int4 blk = blocks[blockIdx.x];
-    const DropDev& D = drops[blk.x];
-    const double n = part_join(D, part, P_CN);
-    const double mx = part_join(D, part, P_CX) / n, my = part_join(D, part, P_CY) / n;
+__device__ __forceinline__ void cross_dist(const DropDev& D, const NodeArrays& A, const Chunk& ch, double zcut) {
+    const double n = part_join(ch, P_CN);
+    const double mx = part_join(ch, P_CX) / n, my = part_join(ch, P_CY) / n;
     double d = 0.0;
-    chunk_tris(D, A, blk.y, [&](const double P[3][3], const int v[3]) {
+    chunk_tris(D, A, ch, [&](const double P[3][3], const int v[3]) {
         edge_crossings(P, v, zcut == zcut ? zcut : D.zcut, [&](double x, double y) {
             d += sqrt((x - mx) * (x - mx) + (y - my) * (y - my));
         });
     });
     const double v[1] = {d};
-    part_put(D, blk, part, P_DIST, v);
+    part_put(ch, P_DIST, v);
 }
 
-// One workgroup per droplet: cell partials + interface partials joined.
-// partials may be null: interface quantities only (cell sums left zero).
-constexpr int kFinalBlock = 1024;
-template <int DIM>
-__global__ __launch_bounds__(kFinalBlock) void k_diag_final(const DropDev* __restrict__ drops,
-                                                            const double* __restrict__ partials,
-                                                            const double* __restrict__ part,
-                                                            DiagDev* __restrict__ out) {
-    constexpr int W = kFinalBlock / 64;
+// Cell partials + interface partials of droplet D joined by a workgroup of
+// BLK lanes.  partials may be null: interface quantities only (cell sums left
+// zero).
+template <int DIM, int BLK>
+__device__ __forceinline__ void diag_final(const DropDev& D, const double* __restrict__ partials, const Chunk& ch,
+                                           DiagDev* __restrict__ out) {
+    constexpr int W = BLK / 64;
     __shared__ double cells[W][7];
     __shared__ double joined[P_SLOTS];
-    const int d = blockIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const DropDev& D = drops[d];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     double acc[7] = {0, 0, 0, 0, 0, 0, 0};
     if (partials)
-        for (int t = D.grp_off + threadIdx.x; t < D.grp_off + D.n_grps; t += kFinalBlock)
+        for (int t = D.grp_off + threadIdx.x; t < D.grp_off + D.n_grps; t += BLK)
 #pragma unroll
             for (int k = 0; k < 7; ++k) acc[k] += partials[(long long)t * 8 + k];
 #pragma unroll
@@ -1998,7 +1991,7 @@ __global__ __launch_bounds__(kFinalBlock) void k_diag_final(const DropDev* __res
     }
     for (int s = w; s < P_FLAT; s += W) {
         // the crossings' slots are written in 3D only
-        const double v = DIM == 3 || s < P_CX ? part_join(D, part, s) : 0.0;
+        const double v = DIM == 3 || s < P_CX ? part_join(ch, s) : 0.0;
         if (lane == 0) joined[s] = v;
     }
     __syncthreads();
@@ -2027,7 +2020,56 @@ __global__ __launch_bounds__(kFinalBlock) void k_diag_final(const DropDev* __res
     r.cross_hi = joined[P_HI];
     r.cross_n = joined[P_CN];
     r.cross_r = DIM == 3 ? joined[P_DIST] / joined[P_CN] : 0.0;
-    out[d] = r;
+    *out = r;
+}
+
+// The chunk of this workgroup from the list of all droplets' chunks, and all
+// chunks of a droplet for the workgroup that joins them.
+__device__ __forceinline__ Chunk chunk_of(const DropDev& D, const int4& blk, double* part) {
+    return Chunk{blk.y, D.n_blks, part + (long long)D.blk_off * P_SLOTS};
+}
+
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_diag_part(const DropDev* __restrict__ drops, NodeArrays A,
+                                                      const int4* __restrict__ blocks, double* __restrict__ part) {
+    const int4 blk = blocks[blockIdx.x];
+    const DropDev& D = drops[blk.x];
+    diag_part<DIM>(D, A, chunk_of(D, blk, part));
+}
+__global__ __launch_bounds__(kBlock) void k_cross_dist(const DropDev* __restrict__ drops, NodeArrays A,
+                                                       const int4* __restrict__ blocks, double zcut,
+                                                       double* __restrict__ part) {
+    const int4 blk = blocks[blockIdx.x];
+    const DropDev& D = drops[blk.x];
+    cross_dist(D, A, chunk_of(D, blk, part), zcut);
+}
+constexpr int kFinalBlock = 1024;
+template <int DIM>
+__global__ __launch_bounds__(kFinalBlock) void k_diag_final(const DropDev* __restrict__ drops,
+                                                            const double* __restrict__ partials, double* part,
+                                                            DiagDev* __restrict__ out) {
+    const DropDev& D = drops[blockIdx.x];
+    diag_final<DIM, kFinalBlock>(D, partials, chunk_of(D, make_int4(0, 0, 0, 0), part), out + blockIdx.x);
+}
+// All of it by one workgroup per droplet that strides over the whole
+// interface: for small ones (at most kFewBlocks chunks), where the launches
+// would take longer than the work (329x234, 625 nodes, diagnostics + contact
+// radius: 86 us against 93.6 us with the launches above).
+constexpr int kFewBlocks = 4;
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_diag_one(const DropDev* __restrict__ drops, NodeArrays A,
+                                                     const double* __restrict__ partials,
+                                                     DiagDev* __restrict__ out) {
+    __shared__ double part[P_SLOTS];
+    const DropDev& D = drops[blockIdx.x];
+    const Chunk ch{0, 1, part};
+    diag_part<DIM>(D, A, ch);
+    __syncthreads();
+    if (DIM == 3) {
+        cross_dist(D, A, ch, __builtin_nan(""));
+        __syncthreads();
+    }
+    diag_final<DIM, kBlock>(D, partials, ch, out + blockIdx.x);
 }
 
 // Contact radius of one droplet at the positions A.pos by the two protocols
@@ -2043,43 +2085,40 @@ __global__ __launch_bounds__(kFinalBlock) void k_diag_final(const DropDev* __res
 // number of crossings to out (20 252 vertices: 219 us on one workgroup, about 25
 // so).
 template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_contact_height(const DropDev* __restrict__ drops, NodeArrays A,
-                                                           const int4* __restrict__ blocks,
-                                                           double* __restrict__ part) {
-    const int4 blk = blocks[blockIdx.x];
-    const DropDev& D = drops[blk.x];
-    const int l = blk.y * kBlock + (int)threadIdx.x;
+__device__ __forceinline__ void contact_height(const DropDev& D, const NodeArrays& A, const Chunk& ch) {
     double hmin = 1e300, hmax = -1e300;
-    if (l < D.n_nodes) hmin = hmax = A.pos[(DIM - 1) * A.stride + D.node_off + l];
+    for (int l = ch.c * kBlock + (int)threadIdx.x; l < D.n_nodes; l += ch.n * kBlock) {
+        const double h = A.pos[(DIM - 1) * A.stride + D.node_off + l];
+        hmin = fmin(hmin, h);
+        hmax = fmax(hmax, h);
+    }
     const double v[2] = {hmin, hmax};
-    part_put(D, blk, part, P_HMIN, v);
+    part_put(ch, P_HMIN, v);
 }
 
 template <int DIM>
-__global__ __launch_bounds__(kBlock) void k_contact_part(const DropDev* __restrict__ drops, NodeArrays A,
-                                                         const int4* __restrict__ blocks, double zcut, double tol,
-                                                         double* __restrict__ part) {
-    const int4 blk = blocks[blockIdx.x];
-    const DropDev& D = drops[blk.x];
+__device__ __forceinline__ void contact_part(const DropDev& D, const NodeArrays& A, const Chunk& ch, double zcut,
+                                             double tol) {
     const int st = A.stride, N = D.n_nodes, j0 = D.node_off;
-    const double hmin = part_join(D, part, P_HMIN), hmax = part_join(D, part, P_HMAX);
+    const double hmin = part_join(ch, P_HMIN), hmax = part_join(ch, P_HMAX);
     const double mid = 0.5 * (hmin + hmax);
     double lo = 1e300, hi = -1e300, cx = 0.0, cy = 0.0, cn = 0.0, flat = 0.0;
     if (DIM == 2) {
-        const int l = blk.y * kBlock + (int)threadIdx.x;
-        if (l < N) {
+        for (int l = ch.c * kBlock + (int)threadIdx.x; l < N; l += ch.n * kBlock) {
             const int j = j0 + l, jp = j0 + (l == N - 1 ? 0 : l + 1);
             const double x0 = A.pos[j], y0 = A.pos[st + j], x1 = A.pos[jp], y1 = A.pos[st + jp];
             const double a0 = y0 - zcut, a1 = y1 - zcut;
             if (a0 * a1 < 0.0 || (a0 == 0.0 && a1 != 0.0)) {
-                lo = hi = x0 + a0 / (a0 - a1) * (x1 - x0);
-                cn = 1.0;
+                const double xs = x0 + a0 / (a0 - a1) * (x1 - x0);
+                lo = fmin(lo, xs);
+                hi = fmax(hi, xs);
+                cn += 1.0;
             }
             if (y0 < mid && y1 < mid && fabs(y1 - y0) < tol)
-                flat = sqrt((x1 - x0) * (x1 - x0) + (y1 - y0) * (y1 - y0));
+                flat += sqrt((x1 - x0) * (x1 - x0) + (y1 - y0) * (y1 - y0));
         }
     } else {
-        chunk_tris(D, A, blk.y, [&](const double P[3][3], const int v[3]) {
+        chunk_tris(D, A, ch, [&](const double P[3][3], const int v[3]) {
             edge_crossings(P, v, zcut, [&](double x, double y) {
                 cx += x;
                 cy += y;
@@ -2091,22 +2130,20 @@ __global__ __launch_bounds__(kBlock) void k_contact_part(const DropDev* __restri
         });
     }
     const double c[5] = {lo, hi, cx, cy, cn}, g[1] = {flat};
-    part_put(D, blk, part, P_LO, c);
-    part_put(D, blk, part, P_FLAT, g);
+    part_put(ch, P_LO, c);
+    part_put(ch, P_FLAT, g);
 }
 
-// One wavefront.
+// By one wavefront.
 template <int DIM>
-__global__ __launch_bounds__(64) void k_contact_final(const DropDev* __restrict__ drops, int d,
-                                                      const double* __restrict__ part, double* __restrict__ out) {
-    const DropDev& D = drops[d];
-    const double cn = part_join(D, part, P_CN), flat = part_join(D, part, P_FLAT);
+__device__ __forceinline__ void contact_final(const Chunk& ch, double* __restrict__ out) {
+    const double cn = part_join(ch, P_CN), flat = part_join(ch, P_FLAT);
     double ri = __builtin_nan("");
     if (DIM == 2) {
-        const double lo = part_join(D, part, P_LO), hi = part_join(D, part, P_HI);
+        const double lo = part_join(ch, P_LO), hi = part_join(ch, P_HI);
         if (cn >= 2.0) ri = 0.5 * (hi - lo);
     } else {
-        const double dist = part_join(D, part, P_DIST);
+        const double dist = part_join(ch, P_DIST);
         if (cn > 0.0) ri = dist / cn;
     }
     if (threadIdx.x == 0) {
@@ -2114,6 +2151,45 @@ __global__ __launch_bounds__(64) void k_contact_final(const DropDev* __restrict_
         out[1] = DIM == 2 ? 0.5 * flat : sqrt(flat / 3.14159265358979323846);
         out[2] = cn;
     }
+}
+
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_contact_height(const DropDev* __restrict__ drops, NodeArrays A,
+                                                           const int4* __restrict__ blocks,
+                                                           double* __restrict__ part) {
+    const int4 blk = blocks[blockIdx.x];
+    const DropDev& D = drops[blk.x];
+    contact_height<DIM>(D, A, chunk_of(D, blk, part));
+}
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_contact_part(const DropDev* __restrict__ drops, NodeArrays A,
+                                                         const int4* __restrict__ blocks, double zcut, double tol,
+                                                         double* __restrict__ part) {
+    const int4 blk = blocks[blockIdx.x];
+    const DropDev& D = drops[blk.x];
+    contact_part<DIM>(D, A, chunk_of(D, blk, part), zcut, tol);
+}
+template <int DIM>
+__global__ __launch_bounds__(64) void k_contact_final(const DropDev* __restrict__ drops, int d, double* part,
+                                                      double* __restrict__ out) {
+    contact_final<DIM>(chunk_of(drops[d], make_int4(0, 0, 0, 0), part), out);
+}
+// One workgroup for a small interface (see k_diag_one).
+template <int DIM>
+__global__ __launch_bounds__(kBlock) void k_contact_one(const DropDev* __restrict__ drops, int d, NodeArrays A,
+                                                        double zcut, double tol, double* __restrict__ out) {
+    __shared__ double part[P_SLOTS];
+    const DropDev& D = drops[d];
+    const Chunk ch{0, 1, part};
+    contact_height<DIM>(D, A, ch);
+    __syncthreads();
+    contact_part<DIM>(D, A, ch, zcut, tol);
+    __syncthreads();
+    if (DIM == 3) {
+        cross_dist(D, A, ch, zcut);
+        __syncthreads();
+    }
+    if (threadIdx.x < 64) contact_final<DIM>(ch, out);
 }
 
 }  // namespace iblb

@@ -42,6 +42,11 @@ struct MlpLayout {
     size_t master, grad, m, v, wb, xb, partial, total;
     size_t dZb[2];  // output-side gradients (bf16) of two consecutive layers, used in turn
     std::vector<size_t> Z, H;  // Z[l]: layer l output (fp32); H[l]: layer l input (bf16)
+    // whole passes in one launch (k_mlp_rows) for narrow networks: the packed
+    // weights, and what a training pass keeps
+    bool rows = false;
+    size_t packed = 0, zbuf = 0, tbuf = 0;
+    MlpRows R;
 };
 
 bool mlp_plan(int L, const int* widths, int B, MlpLayout& Y, std::string& err) {
@@ -79,7 +84,33 @@ bool mlp_plan(int L, const int* widths, int B, MlpLayout& Y, std::string& err) {
     }
     Y.xb = Y.H[0];
     for (int h = 0; h < 2; ++h) Y.dZb[h] = take(2ull * B * Y.maxw);
-    Y.partial = take(8ull * mlp_cdiv(Y.w[L], 64) * mlp_cdiv(B, kColsumRows));
+    Y.partial = take(8ull * std::max(mlp_cdiv(Y.w[L], 64) * mlp_cdiv(B, kColsumRows), mlp_cdiv(B, kRows)));
+    Y.rows = true;
+    for (int l = 0; l < L; ++l) Y.rows = Y.rows && Y.w[l] <= kRowsWidth;
+    if (Y.rows) {
+        MlpRows& R = Y.R;
+        R.L = L;
+        R.batch = 0;
+        R.ld = mlp_cdiv(B, kRows) * kRows;
+        long long pk = 0, z = 0, t = 0;
+        for (int l = 0; l <= L; ++l) R.w[l] = Y.w[l];
+        for (int l = 0; l < L; ++l) {
+            R.boff[l] = Y.boff[l];
+            R.wp[l] = pk;
+            pk += 8 * packed_pieces(Y.w[l], Y.w[l + 1]);
+            R.wt[l] = pk;
+            pk += 8 * packed_pieces(Y.w[l + 1], Y.w[l]);
+            R.z[l] = z;
+            if (l < L - 1) z += R.ld * kRowsWidth;
+            R.ht[l] = t;
+            t += R.ld * Y.w[l];
+            R.dt[l] = t;
+            t += R.ld * Y.w[l + 1];
+        }
+        Y.packed = take(2ull * pk);
+        Y.zbuf = take(4ull * z);
+        Y.tbuf = take(2ull * t);
+    }
     Y.total = o;
     return true;
 }
@@ -172,6 +203,72 @@ void gemm(const iblb_mlp* c, const Operand& A, const Operand& B, float* Cf, uint
     const int avec = pieces_ok(A, A.t == 0 ? K : M), bvec = pieces_ok(B, B.t == 0 ? K : N);
     const dim3 grid((unsigned)mlp_cdiv(N, 64), (unsigned)mlp_cdiv(M, 64), (unsigned)splits);
     launch_gemm<KP>(c, grid, A, B, Cf, Hb, ldc, bias, Zpre, colsum, M, N, K, act, kc, avec, bvec);
+}
+
+// The packed copies of the weights, from the bf16 one.
+void pack_weights(const iblb_mlp* c) {
+    const MlpLayout& Y = c->Y;
+    if (!Y.rows) return;
+    MlpPack P;
+    long long most = 0;
+    for (int l = 0; l <= Y.L; ++l) P.w[l] = Y.w[l];
+    for (int l = 0; l < Y.L; ++l) {
+        P.woff[l] = Y.woff[l];
+        P.wp[l] = Y.R.wp[l];
+        P.wt[l] = Y.R.wt[l];
+        most = std::max(most, packed_pieces(Y.w[l], Y.w[l + 1]) + packed_pieces(Y.w[l + 1], Y.w[l]));
+    }
+    hipLaunchKernelGGL(k_pack, dim3((unsigned)mlp_cdiv(most, kMlpBlock), (unsigned)Y.L), dim3(kMlpBlock), 0, c->stream,
+                       P, (const uint16_t*)c->at<uint16_t>(Y.wb), c->at<uint16_t>(Y.packed));
+}
+
+// The whole forward pass in one launch (narrow networks): enough workgroups
+// per 32 rows to fill the device, at most one per 128 columns of the last
+// layer (a wavefront per two tiles).
+int rows_forward(iblb_mlp* c, const float* d_x, int batch, float* d_y) {
+    const MlpLayout& Y = c->Y;
+    MlpRows P = Y.R;
+    P.batch = batch;
+    const long long nb = mlp_cdiv(batch, kRows);
+    const long long shares = std::max(1LL, std::min(mlp_cdiv(256, nb), mlp_cdiv(Y.w[Y.L], 128)));
+    hipLaunchKernelGGL(k_mlp_rows<0>, dim3((unsigned)nb, (unsigned)shares), dim3(kRowsBlock), 0, c->stream, P, d_x,
+                       (const uint16_t*)c->at<uint16_t>(Y.packed), (const float*)c->at<float>(Y.master), d_y, nullptr,
+                       nullptr, nullptr, nullptr, nullptr);
+    MLPCHK(c, hipGetLastError());
+    return IBLB_OK;
+}
+
+// Forward and backward pass of a narrow network: the activations and the
+// gradients through them in one launch, the weight gradients of all layers
+// in another (about 1024 workgroups, their batch ranges multiples of the LDS
+// panel).
+void rows_gradients(iblb_mlp* c, const float* d_x, const float* d_t, int batch, int nblk) {
+    const MlpLayout& Y = c->Y;
+    MlpRows P = Y.R;
+    P.batch = batch;
+    float* grad = c->at<float>(Y.grad);
+    uint16_t* tbuf = c->at<uint16_t>(Y.tbuf);
+    hipLaunchKernelGGL(k_mlp_rows<1>, dim3((unsigned)nblk), dim3(kRowsBlock), 0, c->stream, P, d_x,
+                       (const uint16_t*)c->at<uint16_t>(Y.packed), (const float*)c->at<float>(Y.master), nullptr, d_t,
+                       c->at<float>(Y.zbuf), tbuf, grad, c->at<double>(Y.partial));
+    MlpWgrad G;
+    G.L = Y.L;
+    G.K = nblk * kRows;
+    G.ld = P.ld;
+    int tiles = 0;
+    for (int l = 0; l <= Y.L; ++l) G.w[l] = Y.w[l];
+    for (int l = 0; l < Y.L; ++l) {
+        G.ht[l] = P.ht[l];
+        G.dt[l] = P.dt[l];
+        G.woff[l] = Y.woff[l];
+        G.tile0[l] = tiles;
+        tiles += (int)(mlp_cdiv(Y.w[l], 64) * mlp_cdiv(Y.w[l + 1], 64));
+    }
+    constexpr int KP = 128;
+    const long long want = std::max(1LL, std::min(mlp_cdiv(1024, tiles), mlp_cdiv(G.K, KP)));
+    G.kc = (int)(mlp_cdiv(mlp_cdiv(G.K, want), KP) * KP);
+    hipLaunchKernelGGL(k_wgrad, dim3((unsigned)tiles, (unsigned)mlp_cdiv(G.K, G.kc)), dim3(kMlpBlock), 0, c->stream, G,
+                       (const uint16_t*)tbuf, grad);
 }
 
 // forward pass of `batch` rows from device fp32 input x
@@ -293,6 +390,7 @@ int iblb_mlp_set_params(iblb_mlp* c, const float* h_params) {
     MLPCHK(c, hipMemsetAsync(c->at<float>(Y.v), 0, 4 * Y.P, c->stream));
     hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)mlp_cdiv(Y.P, kMlpBlock)), dim3(kMlpBlock), 0, c->stream,
                        (const float*)c->at<float>(Y.master), c->at<uint16_t>(Y.wb), Y.P);
+    pack_weights(c);
     MLPCHK(c, hipGetLastError());
     MLPCHK(c, hipStreamSynchronize(c->stream));
     c->t = 0;
@@ -312,6 +410,7 @@ int iblb_mlp_forward(iblb_mlp* c, const float* d_x, int batch, float* d_y) {
     int rc = check_batch(c, batch);
     if (rc) return rc;
     if (!d_x || !d_y) return mlp_fail(c, IBLB_EINVAL, "NULL input or output");
+    if (c->Y.rows) return rows_forward(c, d_x, batch, d_y);
     if ((rc = mlp_forward(c, d_x, batch))) return rc;
     const MlpLayout& Y = c->Y;
     MLPCHK(c, hipMemcpyAsync(d_y, c->at<float>(Y.Z[Y.L - 1]), 4ull * batch * Y.w[Y.L],
@@ -333,6 +432,7 @@ int iblb_mlp_forward_noalloc(iblb_mlp* c, const float* d_x, int batch, float* d_
                  batch, need, kNoallocScratchBytes);
         return mlp_fail(c, IBLB_EINVAL, buf);
     }
+    if (Y.rows) return rows_forward(c, d_x, batch, d_y);  // needs no scratch
     // carve the scratch: bf16 input, fp32 pre-activations, two bf16
     // activation buffers used in turn (no clearing needed: every kernel
     // writes each element it later reads)
@@ -366,37 +466,41 @@ int iblb_mlp_gradients(iblb_mlp* c, const float* d_x, const float* d_t, int batc
     int rc = check_batch(c, batch);
     if (rc) return rc;
     if (!d_x || !d_t) return mlp_fail(c, IBLB_EINVAL, "NULL input or target");
-    if ((rc = mlp_forward(c, d_x, batch))) return rc;
     const MlpLayout& Y = c->Y;
     const int L = Y.L;
     const long long ny = (long long)batch * Y.w[L];
     const dim3 lgrid((unsigned)mlp_cdiv(Y.w[L], 64), (unsigned)mlp_cdiv(batch, kColsumRows));
-    const int nblk = (int)(lgrid.x * lgrid.y);
+    const int nblk = Y.rows ? (int)mlp_cdiv(batch, kRows) : (int)(lgrid.x * lgrid.y);
     float* grad = c->at<float>(Y.grad);
+    if (!Y.rows && (rc = mlp_forward(c, d_x, batch))) return rc;
     // the gradients of every layer are accumulated atomically: zeroed first
     hipLaunchKernelGGL(k_zero_f32, dim3((unsigned)mlp_cdiv(Y.P, kMlpBlock)), dim3(kMlpBlock), 0, c->stream, grad,
                        Y.P);
-    // dZ of layer l lives in buffer (L - 1 - l) % 2; the loss gradient also
-    // gives the last layer's bias gradient
-    hipLaunchKernelGGL(k_mse_colsum, lgrid, dim3(kColsumBlock), 0, c->stream,
-                       (const float*)c->at<float>(Y.Z[L - 1]), d_t, c->at<uint16_t>(Y.dZb[0]),
-                       grad + Y.boff[L - 1], c->at<double>(Y.partial), batch, Y.w[L]);
-    for (int l = L - 1; l >= 0; --l) {
-        const int in = Y.w[l], out = Y.w[l + 1];
-        const int h = (L - 1 - l) & 1;
-        const uint16_t* dZb = c->at<uint16_t>(Y.dZb[h]);
-        // bias: the column sums of dZ, formed with dZ itself (k_mse_colsum,
-        // or the epilogue of the product that forms it); weights: H^T dZ
-        // (K = batch, split over workgroups); input side: dZ W^T, times
-        // GELU'(Z) of the layer below
-        gemm(c, {c->at<uint16_t>(Y.H[l]), in, 1}, {dZb, out, 1}, grad + Y.woff[l], nullptr, out, nullptr, nullptr,
-             in, out, batch, 0, true);
-        if (l > 0)
-            // (dZ of the layer below is needed in bf16 only: its column sums
-            // are formed here)
-            gemm(c, {dZb, out, 0}, {c->at<uint16_t>(Y.wb) + Y.woff[l], out, 0}, nullptr,
-                 c->at<uint16_t>(Y.dZb[h ^ 1]), in, nullptr, c->at<float>(Y.Z[l - 1]), batch, in, out, 2, false,
-                 grad + Y.boff[l - 1]);
+    if (Y.rows) {
+        rows_gradients(c, d_x, d_t, batch, nblk);
+    } else {
+        // dZ of layer l lives in buffer (L - 1 - l) % 2; the loss gradient also
+        // gives the last layer's bias gradient
+        hipLaunchKernelGGL(k_mse_colsum, lgrid, dim3(kColsumBlock), 0, c->stream,
+                           (const float*)c->at<float>(Y.Z[L - 1]), d_t, c->at<uint16_t>(Y.dZb[0]),
+                           grad + Y.boff[L - 1], c->at<double>(Y.partial), batch, Y.w[L]);
+        for (int l = L - 1; l >= 0; --l) {
+            const int in = Y.w[l], out = Y.w[l + 1];
+            const int h = (L - 1 - l) & 1;
+            const uint16_t* dZb = c->at<uint16_t>(Y.dZb[h]);
+            // bias: the column sums of dZ, formed with dZ itself (k_mse_colsum,
+            // or the epilogue of the product that forms it); weights: H^T dZ
+            // (K = batch, split over workgroups); input side: dZ W^T, times
+            // GELU'(Z) of the layer below
+            gemm(c, {c->at<uint16_t>(Y.H[l]), in, 1}, {dZb, out, 1}, grad + Y.woff[l], nullptr, out, nullptr, nullptr,
+                 in, out, batch, 0, true);
+            if (l > 0)
+                // (dZ of the layer below is needed in bf16 only: its column sums
+                // are formed here)
+                gemm(c, {dZb, out, 0}, {c->at<uint16_t>(Y.wb) + Y.woff[l], out, 0}, nullptr,
+                     c->at<uint16_t>(Y.dZb[h ^ 1]), in, nullptr, c->at<float>(Y.Z[l - 1]), batch, in, out, 2, false,
+                     grad + Y.boff[l - 1]);
+        }
     }
     MLPCHK(c, hipGetLastError());
     c->last_batch = batch;
@@ -427,6 +531,7 @@ int iblb_mlp_adam_step(iblb_mlp* c, float lr, float beta1, float beta2, float ep
     hipLaunchKernelGGL(k_adam, dim3((unsigned)mlp_cdiv(Y.P, kMlpBlock)), dim3(kMlpBlock), 0, c->stream,
                        c->at<float>(Y.master), c->at<uint16_t>(Y.wb), (const float*)c->at<float>(Y.grad),
                        c->at<float>(Y.m), c->at<float>(Y.v), Y.P, lr, beta1, beta2, eps, bc1, bc2);
+    pack_weights(c);
     MLPCHK(c, hipGetLastError());
     return IBLB_OK;
 }

@@ -112,17 +112,17 @@ __device__ __forceinline__ void panel_stash(uint16_t* __restrict__ S, int v, u32
 }
 
 template <int AT, int BT, int KP>
-__global__ __launch_bounds__(kMlpBlock) void k_gemm_bf16(
+__device__ __forceinline__ void gemm_tile(
     const uint16_t* __restrict__ A, long long lda, const uint16_t* __restrict__ B, long long ldb,
     float* __restrict__ Cf, uint16_t* __restrict__ Hb, long long ldc, const float* __restrict__ bias,
     const float* __restrict__ Zpre, float* __restrict__ colsum, int M, int N, int K, int act, int kc,
-    int avec, int bvec) {
+    int avec, int bvec, int bx, int by, int bz, bool split) {
     constexpr int LD = KP + 8, NV = KP / 32;
     __shared__ __attribute__((aligned(16))) uint16_t As[64 * LD];
     __shared__ __attribute__((aligned(16))) uint16_t Bs[64 * LD];
     const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-    const int ib = blockIdx.y * 64, jb = blockIdx.x * 64;
-    const int kbeg = blockIdx.z * kc, kend = K < kbeg + kc ? K : kbeg + kc;
+    const int ib = by * 64, jb = bx * 64;
+    const int kbeg = bz * kc, kend = K < kbeg + kc ? K : kbeg + kc;
     const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32;
     f32x16 acc;
 #pragma unroll
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kMlpBlock) void k_gemm_bf16(
     }
     const int j = jb + wj + (lane & 31);
     if (j >= N) return;
-    if (gridDim.z > 1) {
+    if (split) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             const int i = ib + wi + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
@@ -194,6 +194,35 @@ __global__ __launch_bounds__(kMlpBlock) void k_gemm_bf16(
         cs += __shfl_xor(cs, 32, 64);
         if (lane < 32) unsafeAtomicAdd(colsum + j, cs);
     }
+}
+
+template <int AT, int BT, int KP>
+__global__ __launch_bounds__(kMlpBlock) void k_gemm_bf16(
+    const uint16_t* __restrict__ A, long long lda, const uint16_t* __restrict__ B, long long ldb,
+    float* __restrict__ Cf, uint16_t* __restrict__ Hb, long long ldc, const float* __restrict__ bias,
+    const float* __restrict__ Zpre, float* __restrict__ colsum, int M, int N, int K, int act, int kc,
+    int avec, int bvec) {
+    gemm_tile<AT, BT, KP>(A, lda, B, ldb, Cf, Hb, ldc, bias, Zpre, colsum, M, N, K, act, kc, avec, bvec,
+                          blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z > 1);
+}
+
+// The weight gradients of every layer in one launch: grad W_l = H_l^T dZ_l
+// over the batch, both operands as k_mlp_rows left them (batch index
+// contiguous, rows beyond the batch zero), added atomically to grad (zeroed
+// beforehand) by the workgroups that share a tile's batch range.  tile0[l]
+// is layer l's first 64x64 tile among all; blockIdx.y: batch range of kc.
+struct MlpWgrad {
+    int L, K, kc;
+    int w[17], tile0[17];
+    long long ld, ht[16], dt[16], woff[16];
+};
+__global__ __launch_bounds__(kMlpBlock) void k_wgrad(MlpWgrad P, const uint16_t* __restrict__ tbuf,
+                                                     float* __restrict__ grad) {
+    int l = 0;
+    while (l + 1 < P.L && (int)blockIdx.x >= P.tile0[l + 1]) ++l;
+    const int t = (int)blockIdx.x - P.tile0[l], in = P.w[l], out = P.w[l + 1], nx = (out + 63) / 64;
+    gemm_tile<0, 0, 128>(tbuf + P.ht[l], P.ld, tbuf + P.dt[l], P.ld, grad + P.woff[l], nullptr, out, nullptr, nullptr,
+                         nullptr, in, out, P.K, 0, P.kc, 1, 1, t % nx, t / nx, blockIdx.y, true);
 }
 
 // The loss gradient of the last layer and its column sums: dY = 2 (Y - T) /
@@ -246,6 +275,289 @@ __global__ __launch_bounds__(kColsumBlock) void k_mse_colsum(const float* __rest
         double q = 0.0;
         for (int k = 0; k < 64; ++k) q += sq[0][k];
         partial[blockIdx.y * gridDim.x + blockIdx.x] = q;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Whole passes of a narrow network (every input and hidden width at most
+// kRowsWidth) in one launch
+// ---------------------------------------------------------------------------
+// A workgroup takes 32 rows of the batch through all layers: their
+// activations stay in LDS (bf16), a wavefront forms a 32x32 tile of a
+// layer's output at a time, and the weights come straight from the caches in
+// the order in which the matrix instruction takes them (packed once, when
+// the weights change).  One launch per layer spent 11-17 us each on one
+// dependent fetch - product - epilogue chain with a workgroup per compute
+// unit: 4096 rows of 4-256-256-256-1280 took 59 us forward and 130 us with
+// the backward pass through the activations, @@ and @@ so.
+//
+// The products take k in the same order, with the same instruction, as
+// k_gemm_bf16: the results are the same bit for bit.
+constexpr int kRowsBlock = 512;             // 8 wavefronts
+constexpr int kRows = 32;                   // batch rows per workgroup
+constexpr int kRowsWidth = 256;             // widest input or hidden layer
+constexpr int kRowsLd = kRowsWidth + 8;     // LDS row, elements
+constexpr int kMaxLayers = 16;
+
+struct MlpRows {
+    int L, batch;
+    int w[kMaxLayers + 1];
+    long long wp[kMaxLayers];    // packed weights of layer l (elements): B(k, j) = W[k][j]
+    long long wt[kMaxLayers];    // packed transposed weights: B(k, j) = W[j][k]
+    long long boff[kMaxLayers];  // biases in the parameter vector
+    // training
+    long long ld;                // row length of the transposed operands below: batch rounded up to 32
+    long long z[kMaxLayers];     // pre-activations of layer l (floats), in the lanes' own order
+    long long ht[kMaxLayers];    // input of layer l, transposed: [w[l]][ld] bf16
+    long long dt[kMaxLayers];    // gradient at the output of layer l, transposed: [w[l + 1]][ld] bf16
+};
+
+// 16-byte pieces of a packed K x N operand: piece ((s NT + t) 64 + lane)
+// holds B(16 s + 8 (lane / 32) + 0..7, 32 t + lane % 32), zero outside.
+__host__ __device__ __forceinline__ long long packed_pieces(int K, int N) {
+    return (long long)((K + 15) / 16) * ((N + 31) / 32) * 64;
+}
+
+// The pieces of n-tile t of a packed operand (NT n-tiles) for k steps s0 to
+// s0 + ks - 1, all requested at once (steps beyond repeat the last), so that
+// they can be in flight while the operand before them is still worked on.
+struct Pieces {
+    u32x4 b[kRowsWidth / 16];
+    __device__ __forceinline__ void load(const u32x4* __restrict__ Bp, int ks, int s0, int t, int NT, int lane) {
+#pragma unroll
+        for (int s = 0; s < kRowsWidth / 16; ++s)
+            b[s] = Bp[((long long)(s0 + (s < ks ? s : ks - 1)) * NT + t) * 64 + lane];
+    }
+    // acc += A B for the 32 rows of A in LDS, k steps 0 to ks - 1
+    __device__ __forceinline__ f32x16 times(f32x16 acc, const uint16_t* __restrict__ A, int ks, int lane) const {
+        const uint16_t* __restrict__ a0 = A + (lane & 31) * kRowsLd + 8 * (lane >> 5);
+#pragma unroll
+        for (int s = 0; s < kRowsWidth / 16; ++s)
+            if (s < ks)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(a0 + 16 * s),
+                                                              __builtin_bit_cast(bf16x8, b[s]), acc, 0, 0, 0);
+        return acc;
+    }
+};
+__device__ __forceinline__ int k_steps(int K) { return (K + 15) / 16; }
+__device__ __forceinline__ int n_tiles(int N) { return (N + 31) / 32; }
+
+// Row of result register r of a 32x32 product.
+__device__ __forceinline__ int result_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+
+// A tile's column j (this lane's 16 rows, as bf16) into the LDS operand and,
+// transposed, into memory: G[j ld + row0 + row] (four consecutive rows are
+// one 8-byte store).
+__device__ __forceinline__ void rows_put(uint16_t* __restrict__ A, int col, int lane, const uint16_t h[16],
+                                         uint16_t* __restrict__ G, bool write) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) A[result_row(r, lane) * kRowsLd + col] = h[r];
+    if (write) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint64_t v = (uint64_t)h[4 * q] | (uint64_t)h[4 * q + 1] << 16 | (uint64_t)h[4 * q + 2] << 32 |
+                               (uint64_t)h[4 * q + 3] << 48;
+            *reinterpret_cast<uint64_t*>(G + 8 * q + 4 * (lane >> 5)) = v;
+        }
+    }
+}
+
+// TRAIN = 0: y = the network's output for x; gridDim.y workgroups share the
+// last layer's columns of the same rows.
+// TRAIN = 1: the loss of y against tgt (partial[block], summed on the host in
+// block order), the gradients at every layer's output and the inputs of
+// every layer (transposed, for k_wgrad), and the bias gradients (column sums,
+// added to grad atomically).
+template <int TRAIN>
+__global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const float* __restrict__ x,
+                                                         const uint16_t* __restrict__ packed,
+                                                         const float* __restrict__ master, float* __restrict__ y,
+                                                         const float* __restrict__ tgt, float* __restrict__ zbuf,
+                                                         uint16_t* __restrict__ tbuf, float* __restrict__ grad,
+                                                         double* __restrict__ partial) {
+    __shared__ __attribute__((aligned(16))) uint16_t buf[2][kRows * kRowsLd];
+    __shared__ double sq[kRowsBlock / 64];
+    // (the wavefront index is the same for all lanes: keep it scalar)
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, L = P.L;
+    const int row0 = blockIdx.x * kRows, M = P.batch;
+    auto fwd = [&](int l) { return reinterpret_cast<const u32x4*>(packed + P.wp[l]); };
+    auto bwd = [&](int l) { return reinterpret_cast<const u32x4*>(packed + P.wt[l]); };
+    const int K = P.w[L - 1], N = P.w[L], NT = n_tiles(N), KS = k_steps(K);  // of the last layer
+    const int t0 = TRAIN ? 0 : (int)((long long)NT * blockIdx.y / gridDim.y);
+    const int t1 = TRAIN ? NT : (int)((long long)NT * (blockIdx.y + 1) / gridDim.y);
+    Pieces B;
+    // request the pieces of layer l's tile of this wavefront (the last layer:
+    // its first tile)
+    auto request = [&](int l) {
+        const int nt = n_tiles(P.w[l + 1]), t = l < L - 1 ? wave : t0 + wave;
+        if (t < nt) B.load(fwd(l), k_steps(P.w[l]), 0, t, nt, lane);
+    };
+    request(0);
+    // the input, rounded to bf16; columns up to the next multiple of 16 and
+    // rows beyond the batch are zero
+    const int K0 = P.w[0], K0p = (K0 + 15) / 16 * 16;
+    for (int e = threadIdx.x; e < kRows * K0p; e += kRowsBlock) {
+        const int r = e / K0p, k = e - r * K0p;
+        const bool in = row0 + r < M && k < K0;
+        const uint16_t v = in ? f32_to_bf16_rne(x[(long long)(row0 + r) * K0 + k]) : (uint16_t)0;
+        buf[0][r * kRowsLd + k] = v;
+        if (TRAIN && k < K0) tbuf[P.ht[0] + k * P.ld + row0 + r] = v;
+    }
+    __syncthreads();
+    f32x16 zero;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+    float* __restrict__ zw = zbuf + ((long long)blockIdx.x * (kRowsWidth / 32) + wave) * 16 * 64 + lane;
+    int cur = 0;
+    for (int l = 0; l < L - 1; ++l) {
+        const int Nl = P.w[l + 1];
+        const bool mine = wave < n_tiles(Nl);
+        f32x16 acc = zero;
+        if (mine) acc = B.times(zero, buf[cur], k_steps(P.w[l]), lane);
+        request(l + 1);
+        if (mine) {
+            const int j = 32 * wave + (lane & 31);
+            const float bj = j < Nl ? master[P.boff[l] + j] : 0.f;
+            uint16_t h[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float z = acc[r] + bj;
+                if (TRAIN) zw[P.z[l] + r * 64] = z;
+                const bool in = j < Nl && (!TRAIN || row0 + result_row(r, lane) < M);
+                h[r] = in ? f32_to_bf16_rne(gelu(z)) : (uint16_t)0;
+            }
+            rows_put(buf[cur ^ 1], j, lane, h, TRAIN ? tbuf + P.ht[l + 1] + (long long)j * P.ld + row0 : nullptr,
+                     TRAIN && j < Nl);
+        }
+        cur ^= 1;
+        __syncthreads();
+    }
+    const uint16_t* __restrict__ H = buf[cur];
+    if (!TRAIN) {
+        for (int t = t0 + wave; t < t1; t += kRowsBlock / 64) {
+            const f32x16 acc = B.times(zero, H, KS, lane);
+            if (t + kRowsBlock / 64 < t1) B.load(fwd(L - 1), KS, 0, t + kRowsBlock / 64, NT, lane);
+            const int j = 32 * t + (lane & 31);
+            const float bj = j < N ? master[P.boff[L - 1] + j] : 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int i = row0 + result_row(r, lane);
+                if (i < M && j < N) y[(long long)i * N + j] = acc[r] + bj;
+            }
+        }
+        return;
+    }
+    // training: the last layer in chunks of kRowsWidth columns; each chunk's
+    // loss gradient is at once multiplied into the gradient at the layer below
+    const float scale = 2.f / (float)((long long)M * N);
+    const int JT = L > 1 ? n_tiles(K) : 0;  // tiles of the layer below
+    __shared__ __attribute__((aligned(16))) uint16_t dy[2][kRows * kRowsLd];
+    f32x16 down = zero;
+    double e2 = 0.0;
+    int par = 0;
+    for (int c = 0; c < N; c += kRowsWidth, par ^= 1) {
+        const int t = c / 32 + wave, j = 32 * t + (lane & 31);
+        const int kc = N - c < kRowsWidth ? N - c : kRowsWidth;
+        Pieces D;  // of the product with the transposed weights
+        if (wave < JT) D.load(bwd(L - 1), k_steps(kc), c / 16, wave, JT, lane);
+        if (t < NT) {
+            // the targets are requested together (elements outside: a valid
+            // one instead, not used)
+            float tv[16];
+            const int jc = j < N ? j : N - 1;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int i = row0 + result_row(r, lane);
+                tv[r] = tgt[(long long)(i < M ? i : M - 1) * N + jc];
+            }
+            const float bj = master[P.boff[L - 1] + jc];
+            const f32x16 acc = B.times(zero, H, KS, lane);
+            if (t + kRowsBlock / 64 < NT) B.load(fwd(L - 1), KS, 0, t + kRowsBlock / 64, NT, lane);
+            uint16_t h[16];
+            float cs = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const bool in = row0 + result_row(r, lane) < M && j < N;
+                const float e = in ? (acc[r] + bj) - tv[r] : 0.f;
+                const float d = scale * e;
+                e2 += (double)e * e;
+                cs += d;
+                h[r] = f32_to_bf16_rne(d);
+            }
+            rows_put(dy[par], 32 * wave + (lane & 31), lane, h, tbuf + P.dt[L - 1] + (long long)j * P.ld + row0, j < N);
+            cs += __shfl_xor(cs, 32, 64);
+            if (lane < 32 && j < N) unsafeAtomicAdd(grad + P.boff[L - 1] + j, cs);
+        }
+        __syncthreads();
+        if (wave < JT) down = D.times(down, dy[par], k_steps(kc), lane);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) e2 += __shfl_xor(e2, o, 64);
+    if (lane == 0) sq[wave] = e2;
+    // gradients at the hidden layers' outputs, from the last one down
+    for (int l = L - 2; l >= 0; --l) {
+        const int Nl = P.w[l + 1], Tl = n_tiles(P.w[l]);
+        const bool mine = wave < n_tiles(Nl);
+        float z[16];
+        if (mine)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) z[r] = zw[P.z[l] + r * 64];
+        if (l > 0 && wave < Tl) B.load(bwd(l), k_steps(Nl), 0, wave, Tl, lane);
+        __syncthreads();  // every wavefront is done with the operand below
+        if (mine) {
+            const int j = 32 * wave + (lane & 31);
+            uint16_t h[16];
+            float cs = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const bool in = j < Nl && row0 + result_row(r, lane) < M;
+                const float g = in ? down[r] * gelu_grad(z[r]) : 0.f;
+                cs += g;
+                h[r] = f32_to_bf16_rne(g);
+            }
+            rows_put(dy[0], j, lane, h, tbuf + P.dt[l] + (long long)j * P.ld + row0, j < Nl);
+            cs += __shfl_xor(cs, 32, 64);
+            if (lane < 32 && j < Nl) unsafeAtomicAdd(grad + P.boff[l] + j, cs);
+        }
+        if (l == 0) break;
+        __syncthreads();
+        if (wave < Tl) down = B.times(zero, dy[0], k_steps(Nl), lane);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double q = 0.0;
+        for (int k = 0; k < kRowsBlock / 64; ++k) q += sq[k];
+        partial[blockIdx.x] = q;
+    }
+}
+
+// The weights of every layer packed for Pieces, both ways, from the
+// bf16 copy wb (row-major [w[l]][w[l + 1]] at woff): one lane per 16-byte
+// piece, layer blockIdx.y.
+struct MlpPack {
+    int w[kMaxLayers + 1];
+    long long woff[kMaxLayers], wp[kMaxLayers], wt[kMaxLayers];
+};
+__global__ __launch_bounds__(kMlpBlock) void k_pack(MlpPack P, const uint16_t* __restrict__ wb,
+                                                    uint16_t* __restrict__ packed) {
+    const int l = blockIdx.y, in = P.w[l], out = P.w[l + 1];
+    const uint16_t* __restrict__ W = wb + P.woff[l];
+    const long long nf = packed_pieces(in, out), nt = packed_pieces(out, in);
+    for (long long v = (long long)blockIdx.x * kMlpBlock + threadIdx.x; v < nf + nt;
+         v += (long long)gridDim.x * kMlpBlock) {
+        const bool tr = v >= nf;  // transposed: B(k, j) = W[j][k]
+        const long long p = tr ? v - nf : v;
+        const int K = tr ? out : in, N = tr ? in : out, NT = (N + 31) / 32;
+        const int lane = (int)(p & 63), t = (int)((p >> 6) % NT), s = (int)((p >> 6) / NT);
+        const int j = 32 * t + (lane & 31), k0 = 16 * s + 8 * (lane >> 5);
+        u32x4 o = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int k = k0 + u;
+            const uint32_t e = (k < K && j < N) ? W[tr ? (long long)j * out + k : (long long)k * out + j] : 0u;
+            o[u >> 1] |= e << (16 * (u & 1));
+        }
+        reinterpret_cast<u32x4*>(packed + (tr ? P.wt[l] : P.wp[l]))[p] = o;
     }
 }
 
