@@ -114,6 +114,17 @@ __host__ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float v) {
     return (uint16_t)(u >> 16);
 }
 
+// The same on the device in one instruction of gfx950 (v_cvt_pk_bf16_f32).
+// Not for a value that was itself narrowed just before: the compiler would
+// merge the two roundings.
+__device__ __forceinline__ uint16_t to_bf16(float v) {
+#ifdef __AMDGCN__
+    return __builtin_bit_cast(uint16_t, (__bf16)v);
+#else
+    return f32_to_bf16_rne(v);
+#endif
+}
+
 __host__ __device__ __forceinline__ float bf16_to_f32(uint16_t h) {
     return __builtin_bit_cast(float, (uint32_t)h << 16);
 }
@@ -125,9 +136,9 @@ struct Codec<ST_BF16> {
     static __device__ __forceinline__ float load_nt(const T* p, int i) {
         return bf16_to_f32(__builtin_nontemporal_load(p + i));
     }
-    static __device__ __forceinline__ void store(T* p, int i, float v) { p[i] = f32_to_bf16_rne(v); }
+    static __device__ __forceinline__ void store(T* p, int i, float v) { p[i] = to_bf16(v); }
     static __device__ __forceinline__ void store_nt(T* p, int i, float v) {
-        __builtin_nontemporal_store(f32_to_bf16_rne(v), p + i);
+        __builtin_nontemporal_store(to_bf16(v), p + i);
     }
     template <int AUX>
     static __device__ __forceinline__ float load_buf(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff = 0) {
@@ -135,7 +146,7 @@ struct Codec<ST_BF16> {
     }
     template <int AUX>
     static __device__ __forceinline__ void store_buf(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff, float v) {
-        __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16_rne(v), r, (int)off, (int)soff, AUX);
+        __builtin_amdgcn_raw_buffer_store_b16(to_bf16(v), r, (int)off, (int)soff, AUX);
     }
     // exchange values are narrowed through fp32 (nearest even at each step)
     static __device__ __forceinline__ T from_double(double v) { return f32_to_bf16_rne((float)v); }

@@ -12,6 +12,10 @@
 //                   accumulation); epilogue: + bias, optional GELU (keeps
 //                   the fp32 pre-activation and writes the bf16
 //                   activation), or the GELU backward dZ = C * GELU'(Z)
+//   k_mlp_rows      a narrow network's whole forward (or forward and backward)
+//                   pass, 32 rows of the batch per workgroup
+//   k_wgrad         the weight gradients of all its layers
+//   k_pack          its weights in the order of the matrix instruction
 //   k_mse_colsum    loss, dY = 2 (Y - T) / (B n) and the last layer's bias
 //                   gradient (column sums of dY): 64 columns x 256 rows
 //                   per workgroup, reduced in LDS, then added atomically
@@ -180,12 +184,12 @@ __device__ __forceinline__ void gemm_tile(
         if (act == 2) {
             const float g = acc[r] * gelu_grad(Zpre[o]);
             if (Cf) Cf[o] = g;
-            Hb[o] = f32_to_bf16_rne(g);
+            Hb[o] = to_bf16(g);
             cs += g;
         } else {
             const float z = acc[r] + bj;
             Cf[o] = z;
-            if (act) Hb[o] = f32_to_bf16_rne(gelu(z));
+            if (act) Hb[o] = to_bf16(gelu(z));
         }
     }
     if (act == 2 && colsum) {
@@ -253,7 +257,7 @@ __global__ __launch_bounds__(kColsumBlock) void k_mse_colsum(const float* __rest
             const long long o = (long long)i * N + j;
             const float e = Y[o] - T[o];
             const float d = scale * e;
-            dYb[o] = f32_to_bf16_rne(d);
+            dYb[o] = to_bf16(d);
             s += d;
             e2 += (double)e * e;
         }
@@ -289,7 +293,9 @@ __global__ __launch_bounds__(kColsumBlock) void k_mse_colsum(const float* __rest
 // the weights change).  One launch per layer spent 11-17 us each on one
 // dependent fetch - product - epilogue chain with a workgroup per compute
 // unit: 4096 rows of 4-256-256-256-1280 took 59 us forward and 130 us with
-// the backward pass through the activations, @@ and @@ so.
+// the backward pass through the activations, 29 and 56 so (64 rows: 43 and
+// 17 us forward).  What is left is the serial chain through the layers, of
+// which the exact GELU of 16 values per lane takes about half.
 //
 // The products take k in the same order, with the same instruction, as
 // k_gemm_bf16: the results are the same bit for bit.
@@ -324,13 +330,24 @@ __host__ __device__ __forceinline__ long long packed_pieces(int K, int N) {
 struct Pieces {
     u32x4 b[kRowsWidth / 16];
     __device__ __forceinline__ void load(const u32x4* __restrict__ Bp, int ks, int s0, int t, int NT, int lane) {
+        const u32x4* __restrict__ p = Bp + ((long long)s0 * NT + t) * 64;
+        const int step = NT * 64;
 #pragma unroll
-        for (int s = 0; s < kRowsWidth / 16; ++s)
-            b[s] = Bp[((long long)(s0 + (s < ks ? s : ks - 1)) * NT + t) * 64 + lane];
+        for (int s = 0; s < kRowsWidth / 16; ++s) {
+            b[s] = p[lane];
+            p += s + 1 < ks ? step : 0;
+        }
     }
     // acc += A B for the 32 rows of A in LDS, k steps 0 to ks - 1
     __device__ __forceinline__ f32x16 times(f32x16 acc, const uint16_t* __restrict__ A, int ks, int lane) const {
         const uint16_t* __restrict__ a0 = A + (lane & 31) * kRowsLd + 8 * (lane >> 5);
+        if (ks == kRowsWidth / 16) {  // (a branch per step would wait for each LDS read in turn)
+#pragma unroll
+            for (int s = 0; s < kRowsWidth / 16; ++s)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(a0 + 16 * s),
+                                                              __builtin_bit_cast(bf16x8, b[s]), acc, 0, 0, 0);
+            return acc;
+        }
 #pragma unroll
         for (int s = 0; s < kRowsWidth / 16; ++s)
             if (s < ks)
@@ -399,7 +416,7 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const float*
     for (int e = threadIdx.x; e < kRows * K0p; e += kRowsBlock) {
         const int r = e / K0p, k = e - r * K0p;
         const bool in = row0 + r < M && k < K0;
-        const uint16_t v = in ? f32_to_bf16_rne(x[(long long)(row0 + r) * K0 + k]) : (uint16_t)0;
+        const uint16_t v = in ? to_bf16(x[(long long)(row0 + r) * K0 + k]) : (uint16_t)0;
         buf[0][r * kRowsLd + k] = v;
         if (TRAIN && k < K0) tbuf[P.ht[0] + k * P.ld + row0 + r] = v;
     }
@@ -424,7 +441,8 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const float*
                 const float z = acc[r] + bj;
                 if (TRAIN) zw[P.z[l] + r * 64] = z;
                 const bool in = j < Nl && (!TRAIN || row0 + result_row(r, lane) < M);
-                h[r] = in ? f32_to_bf16_rne(gelu(z)) : (uint16_t)0;
+                const uint16_t v = to_bf16(gelu(z));
+                h[r] = in ? v : (uint16_t)0;
             }
             rows_put(buf[cur ^ 1], j, lane, h, TRAIN ? tbuf + P.ht[l + 1] + (long long)j * P.ld + row0 : nullptr,
                      TRAIN && j < Nl);
@@ -482,7 +500,7 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const float*
                 const float d = scale * e;
                 e2 += (double)e * e;
                 cs += d;
-                h[r] = f32_to_bf16_rne(d);
+                h[r] = to_bf16(d);
             }
             rows_put(dy[par], 32 * wave + (lane & 31), lane, h, tbuf + P.dt[L - 1] + (long long)j * P.ld + row0, j < N);
             cs += __shfl_xor(cs, 32, 64);
@@ -511,9 +529,10 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const float*
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const bool in = j < Nl && row0 + result_row(r, lane) < M;
-                const float g = in ? down[r] * gelu_grad(z[r]) : 0.f;
+                const float gz = down[r] * gelu_grad(z[r]);
+                const float g = in ? gz : 0.f;
                 cs += g;
-                h[r] = f32_to_bf16_rne(g);
+                h[r] = to_bf16(g);
             }
             rows_put(dy[0], j, lane, h, tbuf + P.dt[l] + (long long)j * P.ld + row0, j < Nl);
             cs += __shfl_xor(cs, 32, 64);
@@ -581,13 +600,13 @@ __global__ void k_adam(float* __restrict__ w, uint16_t* __restrict__ wb, const f
     v[i] = vi;
     const float wi = w[i] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
     w[i] = wi;
-    wb[i] = f32_to_bf16_rne(wi);
+    wb[i] = to_bf16(wi);
 }
 
 // fp32 -> bf16 (nearest even), n elements
 __global__ void k_to_bf16(const float* __restrict__ x, uint16_t* __restrict__ y, long long n) {
     const long long i = (long long)blockIdx.x * kMlpBlock + threadIdx.x;
-    if (i < n) y[i] = f32_to_bf16_rne(x[i]);
+    if (i < n) y[i] = to_bf16(x[i]);
 }
 
 }  // namespace iblb
