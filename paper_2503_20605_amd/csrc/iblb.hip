@@ -691,13 +691,13 @@ void launch_pop_io(iblb_ctx* c, int d, const double* in, double* out) {
     using T = typename Codec<S>::T;
     T* f = c->at<T>(c->cur ? c->L.f1 : c->L.f0) + c->drops[d].f_off;
     const DropDev& D = c->drops[d];
-    const long long n = (long long)c->Q * D.ncell;
+    const int nxy = D.nx * D.ny;
+    const dim3 grid(ceil_div(nxy, kPopCells), std::min(D.nz, 65535), c->Q);
     if (in)
-        hipLaunchKernelGGL(k_pop_write<S>, dim3(ceil_div(n, kBlock)), dim3(kBlock), 0, c->stream, f,
-                           D.ncell, D.fst, D.nx * D.ny, D.ppl, n, in);
+        hipLaunchKernelGGL(k_pop_write<S>, grid, dim3(kBlock), 0, c->stream, f, D.ncell, D.fst, nxy, D.ppl, D.nz, in);
     else
-        hipLaunchKernelGGL(k_pop_read<S>, dim3(ceil_div(n, kBlock)), dim3(kBlock), 0, c->stream,
-                           (const T*)f, D.ncell, D.fst, D.nx * D.ny, D.ppl, n, out);
+        hipLaunchKernelGGL(k_pop_read<S>, grid, dim3(kBlock), 0, c->stream, (const T*)f, D.ncell, D.fst, nxy, D.ppl,
+                           D.nz, out);
 }
 
 int pop_io(iblb_ctx* c, int d, const double* in, double* out) {

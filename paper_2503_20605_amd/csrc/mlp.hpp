@@ -424,7 +424,8 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const float*
     f32x16 zero;
 #pragma unroll
     for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-    float* __restrict__ zw = zbuf + ((long long)blockIdx.x * (kRowsWidth / 32) + wave) * 16 * 64 + lane;
+    float* __restrict__ zw =
+        TRAIN ? zbuf + ((long long)blockIdx.x * (kRowsWidth / 32) + wave) * 16 * 64 + lane : nullptr;
     int cur = 0;
     for (int l = 0; l < L - 1; ++l) {
         const int Nl = P.w[l + 1];
