@@ -110,7 +110,7 @@ constexpr int kPlanePad = IBLB_PLANE_PAD;
 // Cell budget of a 3D spreading chunk's tap box when the host cuts chunks
 // (see morton_order); the kernel's own limit is kBoxCells.
 #ifndef IBLB_CHUNK_BUDGET
-#define IBLB_CHUNK_BUDGET 640
+#define IBLB_CHUNK_BUDGET 1200
 #endif
 
 // Band flags per lattice row: one byte per strip of Strip<dim, storage>::n
@@ -623,7 +623,7 @@ void launch_after(const iblb_ctx* c, hipStream_t s, int p, bool last, int want_d
                            U, c->at<int>(c->L.status));
     else
         hipLaunchKernelGGL((one ? k_interp_advect<3, true> : k_interp_advect<3, false>),
-                           dim3(ceil_div(c->L.ntot * InterpLanes<3>::n, kNodeBlock)), block, 0, s, D, A, U,
+                           dim3(ceil_div(c->L.ntot * InterpLanes<3>::n, interp_block<3>())), dim3(interp_block<3>()), 0, s, D, A, U,
                            c->at<int>(c->L.status));
     if (!last) launch_spread(c, s, p ^ 1, want_dropped);
 }

@@ -125,8 +125,11 @@ struct DiagDev {
 constexpr double kFqScale = 1099511627776.0;  // 2^40
 constexpr float kFqMax = 1024.f;
 __device__ __forceinline__ bool fq_ok(float v) { return fabsf(v) < kFqMax; }  // NaN: false
+// rint(v 2^40) as a 64-bit integer: adding 1.5 2^52 rounds to a whole number
+// (nearest even) and leaves it in the low bits of the sum; |v 2^40| < 2^50.
 __device__ __forceinline__ unsigned long long fq_of(float v) {
-    return (unsigned long long)(long long)rint((double)v * kFqScale);
+    const double m = __builtin_fma((double)v, kFqScale, 6755399441055744.0);
+    return __builtin_bit_cast(unsigned long long, m) - 0x4338000000000000ull;
 }
 __device__ __forceinline__ float fq_value(unsigned long long v) {
     return (float)((double)(long long)v * (1.0 / kFqScale));
@@ -538,11 +541,14 @@ __device__ __forceinline__ bool coord_ok(double v) { return fabs(v) <= kFarCoord
 // axis, -1 beyond a wall.  base comes from a coordinate that passed coord_ok,
 // so base + k cannot overflow.
 __device__ __forceinline__ int tap_index(int base, int k, int n, int wall) {
-    int i = base + k;
-    if (i >= 0 && i < n) return i;
-    if (wall) return -1;
-    i %= n;
-    return i < 0 ? i + n : i;
+    const int i = base + k;
+    const bool out = (unsigned)i >= (unsigned)n;
+    int w = i < 0 ? i + n : i - n;  // a node within a period of the box
+    if (out && !wall && (unsigned)w >= (unsigned)n) {
+        w = i % n;
+        w = w < 0 ? w + n : w;
+    }
+    return out ? (wall ? -1 : w) : i;
 }
 
 struct NodeArrays {
@@ -808,13 +814,19 @@ struct Taps {
     static constexpr int n = DIM == 2 ? 16 : 64;
 };
 
-// Lanes per node of the interpolation kernel: one per tap in 2D; in 3D two
-// taps per lane, so the 64 taps of a vertex take half a wavefront and a
-// batch of vertices half as many wavefronts.
+// Lanes per node of the interpolation kernel: one per tap in 2D; in 3D four
+// taps per lane (those of a column of the stencil), 16 lanes per vertex, so
+// that a lane forms its x and y weights once for four gathers.  80x80x60 /
+// 256x256x128 / 240x240x130 (40 962 vertices): 6.9 / 8.5 / 16.1 us per launch
+// against 8.5 / 9.5 / 19.1 us with two taps per lane.
 template <int DIM>
 struct InterpLanes {
-    static constexpr int n = DIM == 3 ? Taps<3>::n / 2 : Taps<2>::n;
+    static constexpr int n = 16;
 };
+// lanes per workgroup of it (3D: 256 lanes 7.7 / 8.9 / 17.1 us against 8.5 /
+// 9.5 / 19.1 us with 64, at two taps per lane)
+template <int DIM>
+constexpr int interp_block() { return DIM == 3 ? kBlock : kNodeBlock; }
 
 // ---------------------------------------------------------------------------
 // Peskin 4-point kernel
@@ -829,14 +841,25 @@ struct InterpLanes {
 //
 // peskin_tap: weight of tap k (0..3) of a node at coordinate q, and the
 // index of tap 0.
+struct PeskinAxis {
+    int base;    // index of tap 0
+    float r, s;
+    __device__ __forceinline__ explicit PeskinAxis(double q) {
+        const double u = q - 0.5;
+        const double fl = floor(u);
+        r = (float)(u - fl);
+        base = (int)fl - 1;
+        s = sqrtf(1.f + 4.f * r * (1.f - r));
+    }
+    __device__ __forceinline__ float weight(int k) const {
+        const float a = k < 2 ? 3.f - 2.f * r : 1.f + 2.f * r;
+        return (a + ((k == 1 || k == 2) ? s : -s)) * 0.125f;
+    }
+};
 __device__ __forceinline__ float peskin_tap(double q, int k, int& base) {
-    const double u = q - 0.5;
-    const double fl = floor(u);
-    const float r = (float)(u - fl);
-    base = (int)fl - 1;
-    const float s = sqrtf(1.f + 4.f * r * (1.f - r));
-    const float a = k < 2 ? 3.f - 2.f * r : 1.f + 2.f * r;
-    return (a + ((k == 1 || k == 2) ? s : -s)) * 0.125f;
+    const PeskinAxis p(q);
+    base = p.base;
+    return p.weight(k);
 }
 
 template <int G>
@@ -1171,17 +1194,20 @@ __global__ __launch_bounds__(kBlock) void k_inside_mask(const DropDev* __restric
 // Interpolation (eq. vel_interpolation) + forward-Euler advection
 // ---------------------------------------------------------------------------
 template <int DIM, bool ONE>
-__global__ __launch_bounds__(kNodeBlock) void k_interp_advect(const DropDev* __restrict__ drops,
+__global__ __launch_bounds__(interp_block<DIM>()) void k_interp_advect(const DropDev* __restrict__ drops,
                                                           NodeArrays A,
                                                           const float* __restrict__ U_all,
                                                           int* __restrict__ status) {
     // G lanes per node, each taking T / G taps (k, k + G, ...)
     constexpr int T = Taps<DIM>::n, G = InterpLanes<DIM>::n, R = T / G;
-    const int gid = blockIdx.x * kNodeBlock + threadIdx.x;
+    const int gid = blockIdx.x * interp_block<DIM>() + threadIdx.x;
     const int j = gid / G, k = gid % G;
     if (j >= A.ntot) return;
     const int d = node_droplet<ONE>(A, j);
     const DropDev& D = drops[d];
+    if constexpr (ONE)
+        wanted(D.nx, D.ny, D.nz, D.bcx, D.bcy, D.bcz, D.ncell, D.c_off, D.active, D.force_mode, D.wetting, A.pos,
+               A.pos_w, A.qdot, U_all, status);
     const int st = A.stride;
     if (!D.active || D.force_mode != 0) {
         hold_position<DIM>(A, j, k);
@@ -1202,10 +1228,24 @@ __global__ __launch_bounds__(kNodeBlock) void k_interp_advect(const DropDev* __r
     const float* __restrict__ U = U_all + (long long)DIM * D.c_off;
     float w[R];
     int cell[R];
+    if constexpr (DIM == 3) {
+        // the taps of a lane share their column: x and y weights once
+        static_assert(G % 16 == 0, "taps of a lane differ in z only");
+        const PeskinAxis px(q[0]), py(q[1]), pz(q[2]);
+        const float wxy = px.weight(k & 3) * py.weight((k >> 2) & 3);
+        const int ix = tap_index(px.base, k & 3, D.nx, D.bcx), iy = tap_index(py.base, (k >> 2) & 3, D.ny, D.bcy);
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        int row, ix;
-        cell[r] = lane_tap<DIM>(D, q, k + r * G, w[r], row, ix);
+        for (int r = 0; r < R; ++r) {
+            const int kz = (k >> 4) + r * (G / 16), iz = tap_index(pz.base, kz, D.nz, D.bcz);
+            w[r] = wxy * pz.weight(kz);
+            cell[r] = (ix | iy | iz) < 0 ? -1 : (iz * D.ny + iy) * D.nx + ix;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            int row, ix;
+            cell[r] = lane_tap<DIM>(D, q, k + r * G, w[r], row, ix);
+        }
     }
     // every gather is issued before any is used: a tap beyond a wall, where
     // the fluid is at rest, reads cell 0 with weight zero
@@ -1216,12 +1256,18 @@ __global__ __launch_bounds__(kNodeBlock) void k_interp_advect(const DropDev* __r
 #pragma unroll
         for (int a = 0; a < DIM; ++a) u[r][a] = U[a * D.ncell + c];
     }
-    float acc[3] = {0.f, 0.f, 0.f};
+    // in 3D taps r and r + 2 first, then the two sums: the order of the tree
+    // over 32 lanes of two taps each
+    float acc[3];
+    float wr[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const float wr = cell[r] >= 0 ? w[r] : 0.f;
+    for (int r = 0; r < R; ++r) wr[r] = cell[r] >= 0 ? w[r] : 0.f;
 #pragma unroll
-        for (int a = 0; a < DIM; ++a) acc[a] += u[r][a] * wr;
+    for (int a = 0; a < DIM; ++a) {
+        if constexpr (DIM == 3)
+            acc[a] = __builtin_fmaf(u[2][a], wr[2], u[0][a] * wr[0]) + __builtin_fmaf(u[3][a], wr[3], u[1][a] * wr[1]);
+        else
+            acc[a] = u[0][a] * wr[0];
     }
 #pragma unroll
     for (int a = 0; a < DIM; ++a) acc[a] = group_sum<G>(acc[a]);
@@ -1322,24 +1368,27 @@ __global__ __launch_bounds__(kBlock) void k_force3(const DropDev* __restrict__ d
 // chunk's taps, and each touched cell then takes one global atomic add per
 // component instead of one per contribution.  A chunk whose box exceeds
 // kBoxCells (vertices far apart) adds straight to global memory.
-// Chunks of 16 vertices, 256-lane workgroups and a 1024-cell box measured
-// fastest among chunks of 8-64 vertices and 128-1024 lanes (3D steps of
-// 256x256x128 and 240x240x130: 295 and 348 us against 312 and 374 us for
-// 64 vertices on 1024 lanes), and again with the 64-bit fixed-point sums
-// (256x256x128 step 271 us against 273-278 us for chunks of 8-32 vertices,
-// 128-512 lanes and boxes of 512-2048 cells).
+// What bounds it: the adds to global memory (more than half of the time with
+// chunks of 16 vertices on 256 lanes), so chunks are as large as one
+// workgroup of 16 wavefronts takes in four rounds.  Kernel time on 80x80x60
+// (20 252 vertices, four per cell face), 256x256x128 (20 252) and 240x240x130
+// (40 962): 17.2 / 19.8 / 33.3 us with 16 vertices, 256 lanes and a 1024-cell
+// box; 12.7 / 14.2 / 26.8 with 32 vertices; 9.9 / 12.0 / 21.8 with 64
+// vertices, 1024 lanes and 1536 cells; 10.8 / 12.0 / 24.2 with 128 vertices
+// and 2048 cells.
 #ifndef IBLB_SPREAD_CHUNK
-#define IBLB_SPREAD_CHUNK 16
+#define IBLB_SPREAD_CHUNK 64
 #endif
 #ifndef IBLB_SPREAD_BOX
-#define IBLB_SPREAD_BOX 1024
+#define IBLB_SPREAD_BOX 1536
 #endif
 #ifndef IBLB_SPREAD_BLOCK
-#define IBLB_SPREAD_BLOCK 256
+#define IBLB_SPREAD_BLOCK 1024
 #endif
 constexpr int kChunk = IBLB_SPREAD_CHUNK;
 constexpr int kBoxCells = IBLB_SPREAD_BOX;
 constexpr int kSpreadBlock = IBLB_SPREAD_BLOCK;  // wavefronts each taking every (block / 64)-th vertex
+static_assert(3 * kChunk <= kSpreadBlock, "a lane per vertex and axis");
 
 __global__ __launch_bounds__(kSpreadBlock) void k_spread3(const DropDev* __restrict__ drops, NodeArrays A,
                                                     const int4* __restrict__ chunks,
@@ -1348,46 +1397,55 @@ __global__ __launch_bounds__(kSpreadBlock) void k_spread3(const DropDev* __restr
                                                     int* __restrict__ status, int want_dropped) {
     __shared__ unsigned long long box[3 * kBoxCells];
     __shared__ uint8_t touched[kBoxCells];
-    __shared__ double sq[kChunk][3];
+    __shared__ float swt[kChunk][3][4];   // weights of the four taps along each axis
+    __shared__ int scell[kChunk][3][4];   // their global index, -1 beyond a wall
+    __shared__ int sbase[kChunk][3];      // index of tap 0, not wrapped
     __shared__ float sph[kChunk][3];
     __shared__ int sok[kChunk];
     __shared__ int lo[3], hi[3];
     const int4 ch = chunks[blockIdx.x];  // (droplet, first index into perm, count, -)
+    const DropDev& D = drops[ch.x];
     const int t = threadIdx.x, st = A.stride, count = ch.z;
     // the chunk's vertices (positions and forces together) are fetched
-    // before the droplet's parameters are checked, not after them
-    double q[3] = {0.0, 0.0, 0.0};
-    float ph[3] = {0.f, 0.f, 0.f};
-    if (t < count) {
-        const int j = A.perm[ch.y + t];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            q[a] = A.pos[a * st + j];
-            ph[a] = A.phi[a * st + j];
-        }
+    // before the droplet's parameters are checked, not after them; lane
+    // 3 v + a takes axis a of vertex v
+    const int v0 = t / 3, a0 = t - 3 * v0;
+    const bool mine = t < 3 * count;
+    double q = 0.0;
+    float ph = 0.f;
+    if (mine) {
+        const int j = A.perm[ch.y + v0];
+        q = A.pos[a0 * st + j];
+        ph = A.phi[a0 * st + j];
     }
-    const DropDev& D = drops[ch.x];
+    wanted(D.nx, D.ny, D.nz, D.nstrip, D.sshift, D.bcx, D.bcy, D.bcz, D.ncell, D.c_off, D.flag_off, D.force_mode,
+           D.active);
     if (!D.active || D.force_mode != 0) return;
+    if (t < kChunk) sok[t] = 1;
     if (t < 3) {
         lo[t] = INT_MAX;
         hi[t] = INT_MIN;
     }
     __syncthreads();
-    if (t < count) {
-        bool ok = true;
+    if (mine && !coord_ok(q)) sok[v0] = 0;
+    __syncthreads();
+    if (mine) {
+        if (sok[v0]) {
+            // every tap's weight and index is formed once per vertex and axis
+            // (formed by each of the 64 tap lanes, they made the kernel wait
+            // for its own arithmetic)
+            const PeskinAxis p(q);
+            const int n = a0 == 0 ? D.nx : (a0 == 1 ? D.ny : D.nz), wall = a0 == 0 ? D.bcx : (a0 == 1 ? D.bcy : D.bcz);
 #pragma unroll
-        for (int a = 0; a < 3; ++a) ok = ok && coord_ok(q[a]);
-        sok[t] = ok;
-        if (ok) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                sq[t][a] = q[a];
-                sph[t][a] = ph[a];
-                const int b = (int)floor(q[a] - 0.5) - 1;
-                atomicMin(&lo[a], b);
-                atomicMax(&hi[a], b);
+            for (int k = 0; k < 4; ++k) {
+                swt[v0][a0][k] = p.weight(k);
+                scell[v0][a0][k] = tap_index(p.base, k, n, wall);
             }
-        } else {
+            sbase[v0][a0] = p.base;
+            sph[v0][a0] = ph;
+            atomicMin(&lo[a0], p.base);
+            atomicMax(&hi[a0], p.base);
+        } else if (a0 == 0) {
             atomicOr(status + ch.x, 4);
         }
     }
@@ -1407,19 +1465,17 @@ __global__ __launch_bounds__(kSpreadBlock) void k_spread3(const DropDev* __restr
     bool fine = true;
     const int k = t & 63;  // tap of this lane; one vertex per wavefront at a time
     const int kx = k & 3, ky = (k >> 2) & 3, kz = k >> 4;
+    const int ktap = (kz * ey + ky) * ex + kx;  // its place in a box
     for (int v = t >> 6; v < count; v += kSpreadBlock / 64) {
         if (!sok[v]) continue;  // the same for the whole wavefront
-        int bx, by, bz;
-        const float w = peskin_tap(sq[v][0], kx, bx) * peskin_tap(sq[v][1], ky, by) *
-                        peskin_tap(sq[v][2], kz, bz);
-        const int gx = tap_index(bx, kx, D.nx, D.bcx), gy = tap_index(by, ky, D.ny, D.bcy),
-                  gz = tap_index(bz, kz, D.nz, D.bcz);
+        const float w = swt[v][0][kx] * swt[v][1][ky] * swt[v][2][kz];
+        const int gx = scell[v][0][kx], gy = scell[v][1][ky], gz = scell[v][2][kz];
         float lost[3] = {0.f, 0.f, 0.f};
         if ((gx | gy | gz) < 0) {
 #pragma unroll
             for (int a = 0; a < 3; ++a) lost[a] = sph[v][a] * w;
         } else if (fits) {
-            const int c = ((bz + kz - lo[2]) * ey + (by + ky - lo[1])) * ex + (bx + kx - lo[0]);
+            const int c = ((sbase[v][2] - lo[2]) * ey + (sbase[v][1] - lo[1])) * ex + (sbase[v][0] - lo[0]) + ktap;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const float val = sph[v][a] * w;
@@ -1454,9 +1510,13 @@ __global__ __launch_bounds__(kSpreadBlock) void k_spread3(const DropDev* __restr
     if (!fine) atomicOr(status + ch.x, 2);
     if (!fits) return;
     __syncthreads();
+    // c / ex and (c / ex) / ey of c < kBoxCells by the reciprocal: exact, the
+    // half keeps the product 2^-11 away from a whole number at least
+    const float rx = 1.f / (float)ex, ry = 1.f / (float)ey;
     for (int c = t; c < ncb; c += kSpreadBlock) {
         if (!touched[c]) continue;
-        const int cx = c % ex, cy = (c / ex) % ey, cz = c / (ex * ey);
+        const int r = (int)(((float)c + 0.5f) * rx), cz = (int)(((float)r + 0.5f) * ry);
+        const int cx = c - r * ex, cy = r - cz * ey;
         // a touched cell received a fluid tap, so none of these is -1
         const int gx = tap_index(lo[0], cx, D.nx, D.bcx), gy = tap_index(lo[1], cy, D.ny, D.bcy),
                   gz = tap_index(lo[2], cz, D.nz, D.bcz);
