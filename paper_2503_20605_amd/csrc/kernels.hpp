@@ -1267,7 +1267,7 @@ __global__ __launch_bounds__(interp_block<DIM>()) void k_interp_advect(const Dro
         if constexpr (DIM == 3)
             acc[a] = __builtin_fmaf(u[2][a], wr[2], u[0][a] * wr[0]) + __builtin_fmaf(u[3][a], wr[3], u[1][a] * wr[1]);
         else
-            acc[a] = u[0][a] * wr[0];
+            acc[a] = __builtin_fmaf(u[0][a], wr[0], 0.f);  // (a bare product would be merged into the sum over lanes)
     }
 #pragma unroll
     for (int a = 0; a < DIM; ++a) acc[a] = group_sum<G>(acc[a]);
