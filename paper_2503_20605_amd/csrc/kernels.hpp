@@ -240,6 +240,8 @@ struct Moments {
     __device__ __forceinline__ void relax(const float* f, float om, float g, Out&& out) const {
 #pragma clang fp contract(off)
         using L = Lattice<DIM>;
+        // bf16 storage takes the rounded 1.5 u^2 (see kFused)
+        const float usq15 = 1.5f * usq;
         float uF = 0.f;
         if (FORCED) {
             uF = DIM == 3 ? __builtin_fmaf(ux, Fx, uy * Fy) : __builtin_fmaf(uy, Fy, ux * Fx);
@@ -247,7 +249,8 @@ struct Moments {
         }
         auto one = [&](int i, float cu, float q, float cF) {
             // f_eq - w = w (rho - 1) + w rho (3 cu + 4.5 cu^2 - 1.5 u^2); q = 4.5 cu^2
-            const float e = __builtin_fmaf(rho, __builtin_fmaf(-1.5f, usq, __builtin_fmaf(3.f, cu, q)), drho);
+            const float m = __builtin_fmaf(3.f, cu, q);
+            const float e = __builtin_fmaf(rho, kFused ? __builtin_fmaf(-1.5f, usq, m) : m - usq15, drho);
             float v = __builtin_fmaf(-om, __builtin_fmaf(-L::w[i], e, f[i]), f[i]);
             if (FORCED)
                 // S_i = (1 - 1/2tau) w_i [3 (c - U).F + 9 (c.U)(c.F)]
