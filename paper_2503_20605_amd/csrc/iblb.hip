@@ -3,7 +3,7 @@
 // One handle owns a batch of droplets.  All device arrays are carved from
 // the caller's workspace.  A time step in 2D is two launches on the
 // caller's stream: k_lb (cells, over a tile list that concatenates every
-// active droplet's tiles) and k_ib_fused2 (nodes: interpolation and
+// active droplet's tiles) and k_ib_fused2 or k_ring2 (nodes: interpolation and
 // advection, then the forces and spreading of the next step); in 3D k_lb,
 // k_interp_advect, (k_cross3,) k_force3 and k_spread3.  The first step of a
 // call spreads its own forces and the last one only interpolates.  Long
@@ -64,7 +64,7 @@ int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 
 struct Layout {
     // byte offsets into the workspace
-    size_t drops, tiles_lb, tiles_all, groups, blocks, part, f0, f1, F, Fq, U, Fout, rho, flags, pos0, pos1, phi, qdot, dropped,
+    size_t drops, tiles_lb, tiles_all, groups, blocks, rings, part, f0, f1, F, Fq, U, Fout, rho, flags, pos0, pos1, phi, qdot, dropped,
         node_drop, tri, inc, inc_beg, inc_end, perm, chunks, status, partials, diag,
         xcnt0, xcnt1, xpos0, xpos1, tref, total;
     int nchunks;           // capacity of the 3D spreading chunk table
@@ -73,6 +73,7 @@ struct Layout {
     int ntot, ttot, max_tiles;
     int nblocks = 0;       // interface chunks of all droplets (see k_diag_part)
     int most_blocks = 0;   // of one droplet
+    int nrings = 0;        // workgroups of k_ring2, 0: k_ib_fused2 (see kRingNodes)
     int group_tiles = 1;   // tiles per group of the cell sums
     int ngroups = 0;
     long long pop_elems;   // sum over droplets of Q * fst
@@ -106,6 +107,12 @@ constexpr long long kPopRound = IBLB_POP_ROUND;
 #define IBLB_PLANE_PAD 64
 #endif
 constexpr int kPlanePad = IBLB_PLANE_PAD;
+
+// Nodes from which on the 2D node kernel is k_ring2 (see there): its three
+// stages take longer than k_ib_fused2's one, 17.2 against 16.5 us per step of
+// 8 droplets (3 700 nodes), and win from 12 on (5 500 nodes:
+// 20.8 against 21.3; 32: 33.9 against 40.5).
+constexpr int kRingNodes = 5120;
 
 // Cell budget of a 3D spreading chunk's tap box when the host cuts chunks
 // (see morton_order); the kernel's own limit is kBoxCells.
@@ -159,6 +166,7 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
     L.max_tiles = 0;
     L.nblocks = 0;
     L.most_blocks = 0;
+    L.nrings = 0;
     L.c_off.assign(n, 0);
     L.f_off.assign(n, 0);
     L.fst.assign(n, 0);
@@ -229,6 +237,7 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
         L.tri_off[d] = L.ttot;
         L.ttot += T;
         L.nblocks += iface_blocks(nn[d], T);
+        if (dim == 2) L.nrings += ceil_div(nn[d], kRingOwn);
         L.most_blocks = std::max(L.most_blocks, iface_blocks(nn[d], T));
         L.row_off[d] = (int)L.rows;
         L.rows += (long long)p.ny * nz;
@@ -242,13 +251,16 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
     const long long C = L.cells;
     const int N = std::max(L.ntot, 1), T = std::max(L.ttot, 1);
     size_t o = 0;
+    if (L.ntot < kRingNodes) L.nrings = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
     L.drops = take(sizeof(DropDev) * n);
     L.tiles_lb = take(sizeof(int4) * L.max_tiles);
-    // all tiles, their groups and the interfaces' chunks: one list, uploaded at once
-    L.tiles_all = take(sizeof(int4) * ((size_t)tiles[0] + L.ngroups + L.nblocks));
+    // all tiles, their groups, the interfaces' chunks and the outlines' pieces:
+    // one list, uploaded at once
+    L.tiles_all = take(sizeof(int4) * ((size_t)tiles[0] + L.ngroups + L.nblocks + L.nrings));
     L.groups = L.tiles_all + sizeof(int4) * tiles[0];
     L.blocks = L.groups + sizeof(int4) * L.ngroups;
+    L.rings = L.blocks + sizeof(int4) * L.nblocks;
     L.part = take(sizeof(double) * P_SLOTS * std::max(L.nblocks, 1));
     L.f0 = take((size_t)L.pop_elems * sb);
     L.f1 = take((size_t)L.pop_elems * sb);
@@ -459,7 +471,7 @@ void push_tiles(const iblb_ctx* c, int d, int shape, std::vector<int4>& v) {
 }
 
 int rebuild_tiles(iblb_ctx* c) {
-    std::vector<int4> all, lb, groups, blocks;
+    std::vector<int4> all, lb, groups, blocks, rings;
     for (int d = 0; d < c->n; ++d) {
         // the list of all tiles (diagnostics) always has shape 0
         DropDev& D = c->drops[d];
@@ -472,6 +484,13 @@ int rebuild_tiles(iblb_ctx* c) {
         D.blk_off = (int)blocks.size();
         D.n_blks = iface_blocks(c->n_nodes[d], c->n_tris[d]);
         for (int b = 0; b < D.n_blks; ++b) blocks.push_back(make_int4(d, b, 0, 0));
+        if (c->L.nrings > 0) {  // the outline in equal pieces of at most kRingOwn nodes
+            const long long N = c->n_nodes[d], np = ceil_div(N, kRingOwn);
+            for (long long b = 0; b < np; ++b) {
+                const int first = (int)(N * b / np);
+                rings.push_back(make_int4(d, first, (int)(N * (b + 1) / np) - first, 0));
+            }
+        }
         if (c->drops[d].active) push_tiles(c, d, shape_of(c->variant), lb);
     }
     if (order_of(c->variant) == 0) {
@@ -483,6 +502,7 @@ int rebuild_tiles(iblb_ctx* c) {
     }
     all.insert(all.end(), groups.begin(), groups.end());
     all.insert(all.end(), blocks.begin(), blocks.end());
+    all.insert(all.end(), rings.begin(), rings.end());
     c->ntiles_lb = (int)lb.size();
     HIPCHK(c, hipMemcpyAsync(c->at<int4>(c->L.tiles_all), all.data(), sizeof(int4) * all.size(),
                              hipMemcpyHostToDevice, c->stream));
@@ -613,9 +633,15 @@ void launch_after(const iblb_ctx* c, hipStream_t s, int p, bool last, int want_d
     const bool one = c->n == 1;
     const float* U = c->at<float>(c->L.U);
     if (c->dim == 2 && !last) {
-        hipLaunchKernelGGL(one ? k_ib_fused2<true> : k_ib_fused2<false>, grid, block, 0, s, D, A, U,
-                           c->at<unsigned long long>(c->L.Fq), band_flags(c, p ^ 1), c->at<int>(c->L.status),
-                           want_dropped, cross_count(c, p ^ 1), cross_x(c, p ^ 1));
+        if (c->L.nrings > 0)
+            hipLaunchKernelGGL(k_ring2, dim3(c->L.nrings), dim3(kRingBlock), 0, s, D, A,
+                               (const int4*)c->at<int4>(c->L.rings), U, c->at<unsigned long long>(c->L.Fq),
+                               band_flags(c, p ^ 1), c->at<int>(c->L.status), want_dropped, cross_count(c, p ^ 1),
+                               cross_x(c, p ^ 1));
+        else
+            hipLaunchKernelGGL(one ? k_ib_fused2<true> : k_ib_fused2<false>, grid, block, 0, s, D, A, U,
+                               c->at<unsigned long long>(c->L.Fq), band_flags(c, p ^ 1), c->at<int>(c->L.status),
+                               want_dropped, cross_count(c, p ^ 1), cross_x(c, p ^ 1));
         return;
     }
     if (c->dim == 2)

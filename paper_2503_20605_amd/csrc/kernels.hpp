@@ -10,8 +10,9 @@
 //                     lattice with the Peskin 4-point kernel (eq. force_spread)
 //   k_interp_advect   lattice velocity interpolated at the nodes (eq.
 //                     vel_interpolation) and forward-Euler advection
-//   k_ib_fused2       2D: interpolation and advection of one step fused with
-//                     the forces and spreading of the next
+//   k_ib_fused2,
+//   k_ring2           2D: interpolation and advection of one step fused with
+//                     the forces and spreading of the next (few nodes; many)
 //   k_force3,
 //   k_spread3         3D: forces one lane per vertex (surface tension, an
 //                     elastic interface's shear part, wetting), then
@@ -1688,6 +1689,281 @@ __global__ __launch_bounds__(kNodeBlock) void k_ib_fused2(const DropDev* __restr
         A.phi[st + j] = ph[1];
     }
     spread_lane<2>(D, A, j, k, qn[1], ph, Fq_all, flags_all, want_dropped, status + d);
+}
+
+// A workgroup takes up to kRingOwn consecutive nodes of one outline and the
+// two neighbours beyond them, four lanes each; a lane takes the four taps of
+// one column of the stencil:
+//   1. every group interpolates at its node;
+//   2. two lanes per node advance it and form its force from the new
+//      positions of its ring neighbours, which the workgroup has at hand (no
+//      grid-wide wait between the halves of a step);
+//   3. every group adds its node's force at the new position to a box of
+//      cells in LDS, which is then added to memory: one add per touched cell
+//      and component instead of one per tap.  A box that would be too large
+//      (nodes far apart) is passed by.
+// For batches of many nodes, where the adds to memory, a third of which meet
+// in the same cells, and after them the arithmetic are what bounds the node
+// kernel: k_ib_fused2 makes an add per tap, interpolates at three nodes per
+// node and forms the geometry in all of its 16 lanes.  256 droplets, 118 645
+// nodes: 83 us per launch with k_ib_fused2; 77 us in stages with 16 lanes per
+// node, 69 us with four (19 us of it left with stores in place of the adds),
+// 31.5 us with the box.  Workgroups of one wavefront need no waits between
+// the stages: 40.4 / 40.8 us with 32 / 64 slots, 36.1 / 40.0 us with 12 / 10.
+// A few thousand nodes finish sooner in k_ib_fused2 (see kRingNodes).
+//
+// The sum over a node's taps starts with the unrounded product of a lane and
+// the rounded one of its partner two rows on (a fused multiply-add), so the
+// sums for the lower and the upper two rows may differ in their last bit, as
+// the lanes' of k_ib_fused2 do.  Each half of the stencil is spread with its
+// own sums (that is what the two lanes of a node are for); the lower half's
+// are the ones that are stored.
+// Reads positions A.pos (step t), writes A.pos_w (step t + 1).
+constexpr int kRingSlots = 16;             // nodes of a workgroup, neighbours included
+constexpr int kRingOwn = kRingSlots - 2;
+constexpr int kRingBlock = 4 * kRingSlots;
+constexpr int kRingBox = 256;              // cells of the box: 14 nodes up to 1.1 apart
+
+__global__ __launch_bounds__(kRingBlock) void k_ring2(const DropDev* __restrict__ drops, NodeArrays A,
+                                                      const int4* __restrict__ rings,
+                                                      const float* __restrict__ U_all,
+                                                      unsigned long long* __restrict__ Fq_all,
+                                                      uint8_t* __restrict__ flags_all,
+                                                      int* __restrict__ status, int want_dropped,
+                                                      int* __restrict__ xcnt,
+                                                      double* __restrict__ xpos) {
+    __shared__ double sq[kRingSlots + 2][2];     // old positions of the nodes and one more at each end
+    __shared__ double sn[2][kRingSlots][2];      // new positions, per half
+    __shared__ float sacc[2][kRingSlots][2];     // interpolated velocities, per half
+    __shared__ float sph[2][kRingSlots][2];      // forces, per half
+    __shared__ uint8_t sok[kRingSlots + 2], sgo[2][kRingSlots];
+    __shared__ unsigned long long box[2][kRingBox];
+    __shared__ uint8_t touched[kRingBox];
+    __shared__ int lo[2], hi[2];  // range of the nodes' first taps
+    const int4 rb = rings[blockIdx.x];  // (droplet, first of its nodes, count, -)
+    const int d = rb.x, count = rb.z;
+    const DropDev& D = drops[d];
+    const int N = D.n_nodes, off = D.node_off, st = A.stride;
+    wanted(D.nx, D.ny, D.nstrip, D.sshift, D.bcx, D.bcy, D.ncell, D.c_off, D.flag_off, D.force_mode, D.active,
+           D.wetting, D.n_exp, D.m_exp, D.sigma, D.A, D.xi, D.visc, D.respace, A.pos, U_all, Fq_all, flags_all);
+    const int t = threadIdx.x, slot = t >> 2, l = t & 3;
+    auto node_of = [&](int e) {  // node of slot e (-1 .. count + 2)
+        int id = rb.y - 1 + e;
+        id = id < 0 ? id + N : id;
+        return off + (id >= N ? id - N : id);
+    };
+    if (!D.active || D.force_mode != 0) {
+        if (slot >= 1 && slot <= count) hold_position<2>(A, node_of(slot), l);
+        return;
+    }
+    for (int c = t; c < kRingBox; c += kRingBlock) {
+        box[0][c] = box[1][c] = 0;
+        touched[c] = 0;
+    }
+    if (t < 2) {
+        lo[t] = INT_MAX;
+        hi[t] = INT_MIN;
+    }
+    // stage 1: a slot beyond the workgroup's nodes, or a node that is not
+    // finite or far off, has no taps
+    const bool live = slot < count + 2;
+    double q[3] = {0.0, 0.0, 0.0};
+    if (live) {
+        const int j = node_of(slot);
+        q[0] = A.pos[j];
+        q[1] = A.pos[st + j];
+    }
+    double qe[2] = {0.0, 0.0};
+    if (t < count + 4) {
+        const int j = node_of(t - 1);
+        qe[0] = A.pos[j];
+        qe[1] = A.pos[st + j];
+    }
+    const bool fine = live && coord_ok(q[0]) && coord_ok(q[1]);
+    float u[4][2] = {}, w[4] = {};
+    if (fine) {
+        const float* __restrict__ U = U_all + 2LL * D.c_off;
+        const PeskinAxis px(q[0]), py(q[1]);
+        const float wx = px.weight(l);
+        const int ix = tap_index(px.base, l, D.nx, D.bcx);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int iy = tap_index(py.base, r, D.ny, D.bcy);
+            // a tap beyond a wall, where the fluid is at rest, reads cell 0
+            // with weight zero
+            const bool in = (ix | iy) >= 0;
+            const int c = in ? iy * D.nx + ix : 0;
+            u[r][0] = U[c];
+            u[r][1] = U[D.ncell + c];
+            w[r] = in ? wx * py.weight(r) : 0.f;
+        }
+    }
+    if (t < count + 4) {
+        sq[t][0] = qe[0];
+        sq[t][1] = qe[1];
+        sok[t] = coord_ok(qe[0]) && coord_ok(qe[1]);
+    }
+    float sum[2][2];  // [half][component]
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+#pragma clang fp contract(off)
+            const int r = 2 * h, o = 2 - r;
+            sum[h][a] = __builtin_fmaf(u[r][a], w[r], u[o][a] * w[o]) +
+                        __builtin_fmaf(u[r + 1][a], w[r + 1], u[o + 1][a] * w[o + 1]);
+            sum[h][a] += __shfl_xor(sum[h][a], 2, 64);
+            sum[h][a] += __shfl_xor(sum[h][a], 1, 64);
+        }
+    if (l < 2) {
+        sacc[l][slot][0] = l == 0 ? sum[0][0] : sum[1][0];
+        sacc[l][slot][1] = l == 0 ? sum[0][1] : sum[1][1];
+    }
+    __syncthreads();
+    // stage 2: a lane per half and slot
+    const int h = t / kRingSlots, n = t % kRingSlots;
+    const bool resp = D.respace != 0.0, moves = h < 2 && n < count + 2;
+    float a0 = 0.f, a1 = 0.f;
+    if (moves) {
+        a0 = sacc[h][n][0];
+        a1 = sacc[h][n][1];
+        double x = sq[n + 1][0] + (double)a0, y = sq[n + 1][1] + (double)a1;
+        if (resp) {
+            double dq[2];
+            const double qa[3] = {sq[n][0], sq[n][1], 0.0}, qm[3] = {sq[n + 1][0], sq[n + 1][1], 0.0},
+                         qb[3] = {sq[n + 2][0], sq[n + 2][1], 0.0};
+            respace_move(D.respace, qa, qm, qb, dq);
+            x += dq[0];
+            y += dq[1];
+        }
+        sn[h][n][0] = x;
+        sn[h][n][1] = y;
+    }
+    __syncthreads();
+    bool go = false;
+    if (moves && n >= 1 && n <= count) {
+        const int j = node_of(n);
+        // the old positions of the node, its neighbours and, with
+        // re-spacing, theirs
+        bool ok = sok[n] && sok[n + 1] && sok[n + 2];
+        if (resp) ok = ok && sok[n - 1] && sok[n + 3];
+        if (!ok) {
+            if (h == 0) {
+                hold_position<2>(A, j, 0);
+                hold_position<2>(A, j, 1);
+                atomicOr(status + d, 4);
+            }
+        } else {
+            const double qn[3][3] = {{sn[h][n - 1][0], sn[h][n - 1][1], 0.0},
+                                     {sn[h][n][0], sn[h][n][1], 0.0},
+                                     {sn[h][n + 1][0], sn[h][n + 1][1], 0.0}};
+            if (h == 0) {
+                A.qdot[j] = a0;
+                A.qdot[st + j] = a1;
+                A.pos_w[j] = qn[1][0];
+                A.pos_w[st + j] = qn[1][1];
+                int bad = 0;
+                if (!(a0 * a0 + a1 * a1 <= 0.09f)) bad |= 2;
+                if (D.wetting && !(qn[1][1] > 0.0)) bad |= 1;
+                if (bad) atomicOr(status + d, bad);
+            }
+            go = true;
+#pragma unroll
+            for (int m = 0; m < 3; ++m) go = go && coord_ok(qn[m][0]) && coord_ok(qn[m][1]);
+            if (!go) {
+                if (h == 0) atomicOr(status + d, 4);
+            } else {
+                // crossings of edge j -> j + 1 at the new positions, for
+                // the next step
+                if (D.visc && h == 0) cross_edge_2d(D, xcnt, xpos, qn[1], qn[2], status, d);
+                double fs[2], nrm[2], chi;
+                geom_2d(D.sigma, qn[0], qn[1], qn[2], fs, nrm, chi);
+                if (D.wetting) {
+                    const double P = wetting_pi(D, qn[1][1]);
+                    fs[0] -= 0.5 * chi * P * nrm[0];
+                    fs[1] -= 0.5 * chi * P * nrm[1];
+                }
+                const float f0 = (float)fs[0], f1 = (float)fs[1];
+                sph[h][n][0] = f0;
+                sph[h][n][1] = f1;
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    const int b = (int)floor(qn[1][a] - 0.5) - 1;
+                    atomicMin(&lo[a], b);
+                    atomicMax(&hi[a], b);
+                }
+                if (h == 0) {
+                    A.phi[j] = f0;
+                    A.phi[st + j] = f1;
+                }
+            }
+        }
+    }
+    if (h < 2) sgo[h][n] = go;
+    __syncthreads();
+    // stage 3
+    const bool any = lo[0] <= hi[0];
+    const int ex = any ? hi[0] - lo[0] + 4 : 0, ey = any ? hi[1] - lo[1] + 4 : 0;
+    const bool boxed = any && (long long)ex * ey <= kRingBox;
+    unsigned long long* __restrict__ Fq = Fq_all + 2LL * D.c_off;
+    float lost[4][2] = {};
+    bool sound = true;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (sgo[h][slot]) {
+            const PeskinAxis px(sn[h][slot][0]), py(sn[h][slot][1]);
+            const float wx = px.weight(l), ph[2] = {sph[h][slot][0], sph[h][slot][1]};
+            const int ix = tap_index(px.base, l, D.nx, D.bcx);
+#pragma unroll
+            for (int r = 2 * h; r < 2 * h + 2; ++r) {
+                const int iy = tap_index(py.base, r, D.ny, D.bcy);
+                const float ws = wx * py.weight(r), v[2] = {ph[0] * ws, ph[1] * ws};
+                if ((ix | iy) < 0) {
+                    lost[r][0] = v[0];
+                    lost[r][1] = v[1];
+                    continue;
+                }
+                const int c = boxed ? (py.base + r - lo[1]) * ex + (px.base + l - lo[0]) : 0;
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    if (!fq_ok(v[a]))
+                        sound = false;
+                    else if (boxed)
+                        atomicAdd(&box[a][c], fq_of(v[a]));
+                    else
+                        atomicAdd(Fq + a * D.ncell + iy * D.nx + ix, fq_of(v[a]));
+                }
+                if (boxed)
+                    touched[c] = 1;
+                else
+                    flags_all[D.flag_off + iy * D.nstrip + (ix >> D.sshift)] = 1;
+            }
+        }
+    }
+    if (!sound) atomicOr(status + d, 2);
+    if (want_dropped) {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+#pragma clang fp contract(off)
+            float v = (lost[0][a] + lost[2][a]) + (lost[1][a] + lost[3][a]);
+            v += __shfl_xor(v, 2, 64);
+            v += __shfl_xor(v, 1, 64);
+            if (l == 0 && sgo[0][slot]) A.dropped[a * st + node_of(slot)] = v;
+        }
+    }
+    if (!boxed) return;
+    __syncthreads();
+    const float rx = 1.f / (float)ex;  // (see k_spread3)
+    for (int c = t; c < ex * ey; c += kRingBlock) {
+        if (!touched[c]) continue;
+        const int cy = (int)(((float)c + 0.5f) * rx), cx = c - cy * ex;
+        // a touched cell received a fluid tap, so neither is -1
+        const int gx = tap_index(lo[0], cx, D.nx, D.bcx), gy = tap_index(lo[1], cy, D.ny, D.bcy);
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+            if (box[a][c] != 0) atomicAdd(Fq + a * D.ncell + gy * D.nx + gx, box[a][c]);
+        flags_all[D.flag_off + gy * D.nstrip + (gx >> D.sshift)] = 1;
+    }
 }
 
 // ---------------------------------------------------------------------------
