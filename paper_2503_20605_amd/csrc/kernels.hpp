@@ -504,9 +504,14 @@ __global__ __launch_bounds__(kBlock) void k_lb(const DropDev* __restrict__ drops
         const auto rd = buffer_of(fdst + (long long)lo * fst, (i == 0 ? 1 : 2) * fst * SB);
         C::template store_buf<NT ? nt_store_policy<S>() : 0>(rd, (unsigned)pc * SB, (unsigned)((i - lo) * fst) * SB, fn);
     };
-    // 2D: one straight path (the branch costs a small box 1 us a step in
-    // instruction fetches); 3D: the source is a branch of the whole wavefront
-    if (DIM == 2 || forced)
+    // 3D, and 2D batches in 16-bit storage: the source is a branch of the
+    // whole wavefront.  Otherwise 2D takes one straight path: the branch
+    // costs a small box 1 us a step in instruction fetches and gives nothing
+    // in fp32 (4 fp32 droplets 14.1 against 14.0 us per step, 32: 47.6 both;
+    // fp16: 8 droplets 16.2 against 16.6, and 151.7 against 157.0 us per
+    // launch for 256).
+    constexpr bool SPLIT = DIM == 3 || (!ONE && S != ST_F32);
+    if (!SPLIT || forced)
         M.template relax<true>(f, om, g, put);
     else
         M.template relax<false>(f, om, g, put);
