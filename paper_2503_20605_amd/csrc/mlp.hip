@@ -39,8 +39,10 @@ struct MlpLayout {
     std::vector<int> w;
     std::vector<long long> woff, boff;  // offsets in the packed parameter vector
     long long P = 0;
-    size_t master, grad, m, v, wb, xb, partial, total;
-    size_t dZb[2];  // output-side gradients (bf16) of two consecutive layers, used in turn
+    size_t master, grad, m, v, wb, partial, total;
+    // layer by layer (wider networks): the input (bf16), the output-side
+    // gradients (bf16) of two consecutive layers, used in turn, and
+    size_t xb = 0, dZb[2] = {0, 0};
     std::vector<size_t> Z, H;  // Z[l]: layer l output (fp32); H[l]: layer l input (bf16)
     // whole passes in one launch (k_mlp_rows) for narrow networks: the packed
     // weights, and what a training pass keeps
@@ -76,17 +78,19 @@ bool mlp_plan(int L, const int* widths, int B, MlpLayout& Y, std::string& err) {
     Y.m = take(4 * Y.P);
     Y.v = take(4 * Y.P);
     Y.wb = take(2 * Y.P);
-    Y.Z.resize(L);
-    Y.H.resize(L);
-    for (int l = 0; l < L; ++l) {
-        Y.Z[l] = take(4ull * B * Y.w[l + 1]);
-        Y.H[l] = take(2ull * B * Y.w[l]);
-    }
-    Y.xb = Y.H[0];
-    for (int h = 0; h < 2; ++h) Y.dZb[h] = take(2ull * B * Y.maxw);
-    Y.partial = take(8ull * std::max(mlp_cdiv(Y.w[L], 64) * mlp_cdiv(B, kColsumRows), mlp_cdiv(B, kRows)));
     Y.rows = true;
     for (int l = 0; l < L; ++l) Y.rows = Y.rows && Y.w[l] <= kRowsWidth;
+    if (!Y.rows) {
+        Y.Z.resize(L);
+        Y.H.resize(L);
+        for (int l = 0; l < L; ++l) {
+            Y.Z[l] = take(4ull * B * Y.w[l + 1]);
+            Y.H[l] = take(2ull * B * Y.w[l]);
+        }
+        Y.xb = Y.H[0];
+        for (int h = 0; h < 2; ++h) Y.dZb[h] = take(2ull * B * Y.maxw);
+    }
+    Y.partial = take(8ull * std::max(mlp_cdiv(Y.w[L], 64) * mlp_cdiv(B, kColsumRows), mlp_cdiv(B, kRows)));
     if (Y.rows) {
         MlpRows& R = Y.R;
         R.L = L;
