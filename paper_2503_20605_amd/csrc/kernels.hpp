@@ -398,15 +398,15 @@ __global__ __launch_bounds__(kBlock) void k_lb(const DropDev* __restrict__ drops
     // The band flag of this cell's strip is requested before the
     // populations: loads return in order, so waiting for the flag then does
     // not wait for the populations, and a band wavefront's F loads overlap
-    // them instead of following them.  A lone 2D droplet's kernel requests
-    // it after them: few of its wavefronts lie in the band, and the others
+    // them instead of following them.  A lone 2D droplet's kernel
+    // in fp32 requests it after them: few of its wavefronts lie in the band, and the others
     // then do not start on a line that the node kernel wrote just before
     // (1024x512: 13.8 against 15.4 us per coupled step; the 256-droplet fp16
     // batch 246 against 236 us).
     // A tiled wavefront reads its strips' flags as one aligned word.
     using SW = typename Strip<DIM, S>::Word;
     constexpr int SPW = Strip<DIM, S>::per64;
-    constexpr bool LATE = DIM == 2 && ONE;
+    constexpr bool LATE = DIM == 2 && ONE && S == ST_F32;
     const long long fi = D.flag_off + (long long)(z * ny + y) * D.nstrip + (x >> Strip<DIM, S>::shift);
     int flag;
     auto get_flag = [&](bool given) {
@@ -504,13 +504,14 @@ __global__ __launch_bounds__(kBlock) void k_lb(const DropDev* __restrict__ drops
         const auto rd = buffer_of(fdst + (long long)lo * fst, (i == 0 ? 1 : 2) * fst * SB);
         C::template store_buf<NT ? nt_store_policy<S>() : 0>(rd, (unsigned)pc * SB, (unsigned)((i - lo) * fst) * SB, fn);
     };
-    // 3D, and 2D batches in 16-bit storage: the source is a branch of the
-    // whole wavefront.  Otherwise 2D takes one straight path: the branch
-    // costs a small box 1 us a step in instruction fetches and gives nothing
-    // in fp32 (4 fp32 droplets 14.1 against 14.0 us per step, 32: 47.6 both;
-    // fp16: 8 droplets 16.2 against 16.6, and 151.7 against 157.0 us per
-    // launch for 256).
-    constexpr bool SPLIT = DIM == 3 || (!ONE && S != ST_F32);
+    // 3D and 16-bit storage: the source is a branch of the whole wavefront.
+    // 2D in fp32 takes one straight path: there the branch costs a small box
+    // 1 us a step in instruction fetches and gives nothing to a large one (4
+    // droplets 14.1 against 14.0 us per step, 32: 47.6 both).  fp16: 256
+    // droplets 151.7 against 157.0 us per launch; with the flag requested
+    // early a lone 128x64 box 8.5 against 8.9 us per step, 8192x4096 without
+    // an interface 214 against 229 us.
+    constexpr bool SPLIT = DIM == 3 || S != ST_F32;
     if (!SPLIT || forced)
         M.template relax<true>(f, om, g, put);
     else
