@@ -385,7 +385,7 @@ int iblb_mlp_set_params(iblb_mlp *mlp, const float *h_params);
 int iblb_mlp_get_params(iblb_mlp *mlp, float *h_params);
 
 /* d_x [batch][widths[0]] -> d_y [batch][widths[n_layers]], device fp32,
- * 1 <= batch <= max_batch. */
+ * 1 <= batch <= max_batch.  d_y may overlap d_x (also below). */
 int iblb_mlp_forward(iblb_mlp *mlp, const float *d_x, int batch, float *d_y);
 
 /* Forward + backward of the mean squared error against d_t [batch][out]
@@ -402,18 +402,21 @@ int iblb_mlp_adam_step(iblb_mlp *mlp, float lr, float beta1, float beta2, float 
 
 /* Forward pass that allocates nothing, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops): the
- * same result as iblb_mlp_forward (same kernels, bit for bit), but the
- * bf16 input and the hidden layers' activations live in a static device
- * array of 8 MiB in the library instead of the handle's workspace, and the
- * last layer writes d_y directly.  d_x [batch][widths[0]] -> d_y
+ * same result as iblb_mlp_forward (bit for bit), but what it keeps on the
+ * device lives in a static array of 8 MiB in the library instead of the
+ * handle's workspace, and the last layer writes d_y directly.  A network
+ * whose input and hidden layers are at most 256 wide keeps nothing there,
+ * except the bf16 input where d_y overlaps d_x; a wider one keeps the bf16
+ * input and the hidden layers' activations.  d_x [batch][widths[0]] -> d_y
  * [batch][widths[n_layers]], device fp32; batch >= 1 and not limited by
  * max_batch, but the batch's scratch (2 batch widths[0] bytes plus
  * 8 batch h bytes, h the widest hidden layer, each part rounded up to 256)
- * must fit the 8 MiB, else EINVAL with the sizes in the message.  Queued
- * on the handle's stream; no allocation, no host synchronisation.  Every
- * call on one device shares that device's array: calls that overlap on a
- * device (several streams or threads) race and must be serialised by the
- * caller. */
+ * must fit the 8 MiB, else EINVAL with the sizes in the message (for every
+ * network, so that a program's largest batch does not depend on the way that
+ * its network takes).  Queued on the handle's stream; no allocation, no host
+ * synchronisation.  Calls on one device that keep something in its array
+ * (see above) race when they overlap (several streams or threads) and must
+ * be serialised by the caller. */
 int iblb_mlp_forward_noalloc(iblb_mlp *mlp, const float *d_x, int batch, float *d_y);
 
 #ifdef __cplusplus

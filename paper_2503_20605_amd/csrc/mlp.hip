@@ -228,16 +228,29 @@ void pack_weights(const iblb_mlp* c) {
 
 // The whole forward pass in one launch (narrow networks): enough workgroups
 // per 32 rows to fill the device, at most one per 128 columns of the last
-// layer (a wavefront per two tiles).
-int rows_forward(iblb_mlp* c, const float* d_x, int batch, float* d_y) {
+// layer (four tiles, one for every other wavefront).  Several workgroups read
+// the same rows of the input: where the output overlaps it, the input is kept
+// in bf16 first, in xb (batch w[0] elements).
+int rows_forward(iblb_mlp* c, const float* d_x, int batch, float* d_y, uint16_t* xb) {
     const MlpLayout& Y = c->Y;
     MlpRows P = Y.R;
     P.batch = batch;
-    const long long nb = mlp_cdiv(batch, kRows);
+    const long long nb = mlp_cdiv(batch, kRows), nx = (long long)batch * Y.w[0], ny = (long long)batch * Y.w[Y.L];
     const long long shares = std::max(1LL, std::min(mlp_cdiv(256, nb), mlp_cdiv(Y.w[Y.L], 128)));
-    hipLaunchKernelGGL(k_mlp_rows<0>, dim3((unsigned)nb, (unsigned)shares), dim3(kRowsBlock), 0, c->stream, P, d_x,
-                       (const uint16_t*)c->at<uint16_t>(Y.packed), (const float*)c->at<float>(Y.master), d_y, nullptr,
-                       nullptr, nullptr, nullptr, nullptr);
+    const uintptr_t x0 = reinterpret_cast<uintptr_t>(d_x), y0 = reinterpret_cast<uintptr_t>(d_y);
+    const bool overlap = x0 < y0 + 4ull * ny && y0 < x0 + 4ull * nx;
+    if (overlap)
+        hipLaunchKernelGGL(k_to_bf16, dim3((unsigned)mlp_cdiv(nx, kMlpBlock)), dim3(kMlpBlock), 0, c->stream, d_x, xb,
+                           nx);
+    auto go = [&](auto kern, auto* x) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)nb, (unsigned)shares), dim3(kRowsBlock), 0, c->stream, P, x,
+                           (const uint16_t*)c->at<uint16_t>(Y.packed), (const float*)c->at<float>(Y.master), d_y,
+                           nullptr, nullptr, nullptr, nullptr, nullptr);
+    };
+    if (overlap)
+        go(k_mlp_rows<0, uint16_t>, (const uint16_t*)xb);
+    else
+        go(k_mlp_rows<0, float>, d_x);
     MLPCHK(c, hipGetLastError());
     return IBLB_OK;
 }
@@ -252,7 +265,7 @@ void rows_gradients(iblb_mlp* c, const float* d_x, const float* d_t, int batch, 
     P.batch = batch;
     float* grad = c->at<float>(Y.grad);
     uint16_t* tbuf = c->at<uint16_t>(Y.tbuf);
-    hipLaunchKernelGGL(k_mlp_rows<1>, dim3((unsigned)nblk), dim3(kRowsBlock), 0, c->stream, P, d_x,
+    hipLaunchKernelGGL((k_mlp_rows<1, float>), dim3((unsigned)nblk), dim3(kRowsBlock), 0, c->stream, P, d_x,
                        (const uint16_t*)c->at<uint16_t>(Y.packed), (const float*)c->at<float>(Y.master), nullptr, d_t,
                        c->at<float>(Y.zbuf), tbuf, grad, c->at<double>(Y.partial));
     MlpWgrad G;
@@ -414,7 +427,8 @@ int iblb_mlp_forward(iblb_mlp* c, const float* d_x, int batch, float* d_y) {
     int rc = check_batch(c, batch);
     if (rc) return rc;
     if (!d_x || !d_y) return mlp_fail(c, IBLB_EINVAL, "NULL input or output");
-    if (c->Y.rows) return rows_forward(c, d_x, batch, d_y);
+    // (the operands of a training pass are free between the calls)
+    if (c->Y.rows) return rows_forward(c, d_x, batch, d_y, c->at<uint16_t>(c->Y.tbuf));
     if ((rc = mlp_forward(c, d_x, batch))) return rc;
     const MlpLayout& Y = c->Y;
     MLPCHK(c, hipMemcpyAsync(d_y, c->at<float>(Y.Z[Y.L - 1]), 4ull * batch * Y.w[Y.L],
@@ -436,7 +450,7 @@ int iblb_mlp_forward_noalloc(iblb_mlp* c, const float* d_x, int batch, float* d_
                  batch, need, kNoallocScratchBytes);
         return mlp_fail(c, IBLB_EINVAL, buf);
     }
-    if (Y.rows) return rows_forward(c, d_x, batch, d_y);  // needs no scratch
+    if (Y.rows) return rows_forward(c, d_x, batch, d_y, reinterpret_cast<uint16_t*>(c->scratch));
     // carve the scratch: bf16 input, fp32 pre-activations, two bf16
     // activation buffers used in turn (no clearing needed: every kernel
     // writes each element it later reads)

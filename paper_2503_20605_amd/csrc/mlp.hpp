@@ -380,13 +380,17 @@ __device__ __forceinline__ void rows_put(uint16_t* __restrict__ A, int col, int 
 }
 
 // TRAIN = 0: y = the network's output for x; gridDim.y workgroups share the
-// last layer's columns of the same rows.
+// last layer's columns of the same rows, and each of them reads the rows of x,
+// so y must not overlap x (X = uint16_t: x already rounded to bf16, see
+// rows_forward).
 // TRAIN = 1: the loss of y against tgt (partial[block], summed on the host in
 // block order), the gradients at every layer's output and the inputs of
 // every layer (transposed, for k_wgrad), and the bias gradients (column sums,
 // added to grad atomically).
-template <int TRAIN>
-__global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const float* __restrict__ x,
+__device__ __forceinline__ uint16_t as_bf16(float v) { return to_bf16(v); }
+__device__ __forceinline__ uint16_t as_bf16(uint16_t v) { return v; }
+template <int TRAIN, typename X>
+__global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const X* __restrict__ x,
                                                          const uint16_t* __restrict__ packed,
                                                          const float* __restrict__ master, float* __restrict__ y,
                                                          const float* __restrict__ tgt, float* __restrict__ zbuf,
@@ -416,7 +420,7 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const float*
     for (int e = threadIdx.x; e < kRows * K0p; e += kRowsBlock) {
         const int r = e / K0p, k = e - r * K0p;
         const bool in = row0 + r < M && k < K0;
-        const uint16_t v = in ? to_bf16(x[(long long)(row0 + r) * K0 + k]) : (uint16_t)0;
+        const uint16_t v = in ? as_bf16(x[(long long)(row0 + r) * K0 + k]) : (uint16_t)0;
         buf[0][r * kRowsLd + k] = v;
         if (TRAIN && k < K0) tbuf[P.ht[0] + k * P.ld + row0 + r] = v;
     }

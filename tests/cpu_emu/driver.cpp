@@ -15,6 +15,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <fstream>
 #include <map>
 #include <sstream>
@@ -54,7 +55,9 @@ static T* buf(size_t count) {
 
 // Network mode: config "mlp 1", "widths a,b,...", "batch B", "lr x";
 // files x.bin [B][w0] f32, t.bin [B][wL] f32, params.bin [P] f32.  Writes
-// y.bin, grads.bin, loss.txt and params_after.bin (after one Adam step).
+// y.bin, grads.bin, loss.txt and params_after.bin (after one Adam step).  With
+// "overlap xoff,yoff" the input and the output also share one buffer, at
+// these offsets (floats): y_overlap.bin and y_overlap_noalloc.bin.
 static int run_mlp(std::map<std::string, std::string>& cfg) {
     std::vector<int> w;
     {
@@ -89,8 +92,23 @@ static int run_mlp(std::map<std::string, std::string>& cfg) {
         return 22;
     }
     save("y.bin", yb, (size_t)B * w[L]);
-    save("grads.bin", gb, P);
     save("params_after.bin", pb, P);
+    if (cfg.count("overlap")) {
+        size_t xo = 0, yo = 0;
+        sscanf(cfg["overlap"].c_str(), "%zu,%zu", &xo, &yo);
+        const size_t ny = (size_t)B * w[L], size = std::max(xo + x.size(), yo + ny);
+        memcpy(pb, prm.data(), 4 * P);
+        if (iblb_mlp_set_params(m, pb)) return 23;
+        for (int noalloc = 0; noalloc < 2; ++noalloc) {
+            float* ob = buf<float>(size);
+            memcpy(ob + xo, x.data(), 4 * x.size());
+            if (noalloc ? iblb_mlp_forward_noalloc(m, ob + xo, B, ob + yo) : iblb_mlp_forward(m, ob + xo, B, ob + yo))
+                return 24;
+            save(noalloc ? "y_overlap_noalloc.bin" : "y_overlap.bin", ob + yo, ny);
+            free(ob);
+        }
+    }
+    save("grads.bin", gb, P);
     FILE* f = fopen((dir + "/loss.txt").c_str(), "w");
     fprintf(f, "%.17g\n", loss);
     fclose(f);

@@ -141,15 +141,18 @@ def run_case(params_list, nodes_list=None, tris_list=None, steps=(1,), storage=0
         return outs
 
 
-def run_mlp(widths, params, x, t, lr=1e-3, timeout=600):
+def run_mlp(widths, params, x, t, lr=1e-3, timeout=600, overlap=None):
     """One forward, one gradient evaluation and one Adam step of the network
-    kernels in the sanitizer build.  Returns (y, grads, loss, params_after)."""
+    kernels in the sanitizer build.  Returns (y, grads, loss, params_after);
+    with overlap = (offset of x, offset of y), floats into one buffer, also
+    the outputs of the two forward calls on it."""
     import build as emu_build
     exe = emu_build.build()
     with tempfile.TemporaryDirectory() as d:
         B = x.shape[0]
         open(os.path.join(d, "config.txt"), "w").write(
-            f"mlp 1\nwidths {','.join(str(w) for w in widths)}\nbatch {B}\nlr {lr}\n")
+            f"mlp 1\nwidths {','.join(str(w) for w in widths)}\nbatch {B}\nlr {lr}\n"
+            + (f"overlap {overlap[0]},{overlap[1]}\n" if overlap else ""))
         np.ascontiguousarray(params, dtype=np.float32).tofile(os.path.join(d, "params.bin"))
         np.ascontiguousarray(x, dtype=np.float32).tofile(os.path.join(d, "x.bin"))
         np.ascontiguousarray(t, dtype=np.float32).tofile(os.path.join(d, "t.bin"))
@@ -163,4 +166,8 @@ def run_mlp(widths, params, x, t, lr=1e-3, timeout=600):
         g = np.fromfile(os.path.join(d, "grads.bin"), dtype=np.float32)
         pa = np.fromfile(os.path.join(d, "params_after.bin"), dtype=np.float32)
         loss = float(open(os.path.join(d, "loss.txt")).read())
+        if overlap:
+            return (y, g, loss, pa) + tuple(
+                np.fromfile(os.path.join(d, n), dtype=np.float32).reshape(B, widths[-1])
+                for n in ("y_overlap.bin", "y_overlap_noalloc.bin"))
         return y, g, loss, pa
