@@ -1046,15 +1046,18 @@ void morton_order(const double* pos, int N, int off, std::vector<int>& perm, int
     // box of kChunkBudget cells (below the kernel's kBoxCells, so that the
     // vertices can move a little before a chunk overflows into the direct
     // path).
-    constexpr long long kChunkBudget = IBLB_CHUNK_BUDGET;
+    // (in doubles: any finite position is accepted, and the product of far
+    // extents has to stay a large number)
+    constexpr double kChunkBudget = IBLB_CHUNK_BUDGET;
     chunks.clear();
-    int blo[3] = {0, 0, 0}, bhi[3] = {0, 0, 0}, first = 0, cnt = 0;
+    double blo[3] = {0, 0, 0}, bhi[3] = {0, 0, 0};
+    int first = 0, cnt = 0;
     for (int r = 0; r < N; ++r) {
         const int k = key[r].second;
-        int b[3];
-        for (int a = 0; a < 3; ++a) b[a] = (int)std::floor(pos[(size_t)a * N + k] - 0.5) - 1;
+        double b[3];
+        for (int a = 0; a < 3; ++a) b[a] = std::floor(pos[(size_t)a * N + k] - 0.5) - 1;
         if (cnt > 0) {
-            long long cells = 1;
+            double cells = 1;
             for (int a = 0; a < 3; ++a) cells *= std::max(bhi[a], b[a]) - std::min(blo[a], b[a]) + 4;
             if (cnt == kChunk || cells > kChunkBudget) {
                 chunks.push_back(make_int4(d, off + first, cnt, 0));

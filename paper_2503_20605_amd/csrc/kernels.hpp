@@ -1460,9 +1460,12 @@ __global__ __launch_bounds__(kSpreadBlock) void k_spread3(const DropDev* __restr
         }
     }
     __syncthreads();
-    const int ex = hi[0] - lo[0] + 4, ey = hi[1] - lo[1] + 4, ez = hi[2] - lo[2] + 4;
+    // without a finite vertex there is no box; each extent (up to 2^25 + 4) is
+    // checked by itself, for their product need not fit 64 bits
     const bool any = lo[0] <= hi[0];
-    const bool fits = any && (long long)ex * ey * ez <= kBoxCells;
+    const int ex = any ? hi[0] - lo[0] + 4 : 0, ey = any ? hi[1] - lo[1] + 4 : 0, ez = any ? hi[2] - lo[2] + 4 : 0;
+    const bool fits = any && ex <= kBoxCells && ey <= kBoxCells && ez <= kBoxCells &&
+                      (long long)ex * ey * ez <= kBoxCells;
     const int ncb = fits ? ex * ey * ez : 0;
     for (int c = t; c < ncb; c += kSpreadBlock) {
         box[c] = 0;
@@ -1475,7 +1478,7 @@ __global__ __launch_bounds__(kSpreadBlock) void k_spread3(const DropDev* __restr
     bool fine = true;
     const int k = t & 63;  // tap of this lane; one vertex per wavefront at a time
     const int kx = k & 3, ky = (k >> 2) & 3, kz = k >> 4;
-    const int ktap = (kz * ey + ky) * ex + kx;  // its place in a box
+    const int ktap = fits ? (kz * ey + ky) * ex + kx : 0;  // its place in the box
     for (int v = t >> 6; v < count; v += kSpreadBlock / 64) {
         if (!sok[v]) continue;  // the same for the whole wavefront
         const float w = swt[v][0][kx] * swt[v][1][ky] * swt[v][2][kz];
