@@ -549,16 +549,16 @@ __device__ __forceinline__ bool coord_ok(double v) { return fabs(v) <= kFarCoord
 
 // Cell index of tap base + k along an axis of n cells: wrapped on a periodic
 // axis, -1 beyond a wall.  base comes from a coordinate that passed coord_ok,
-// so base + k cannot overflow.
+// so base + k cannot overflow.  Almost every tap lies in the box: they leave
+// first, the wavefront's others take the branches (selects in their place
+// made the node kernels slower: 128x64 7.5 against 7.4, 1024x512 14.1 against
+// 13.9 us per coupled step).
 __device__ __forceinline__ int tap_index(int base, int k, int n, int wall) {
-    const int i = base + k;
-    const bool out = (unsigned)i >= (unsigned)n;
-    int w = i < 0 ? i + n : i - n;  // a node within a period of the box
-    if (out && !wall && (unsigned)w >= (unsigned)n) {
-        w = i % n;
-        w = w < 0 ? w + n : w;
-    }
-    return out ? (wall ? -1 : w) : i;
+    int i = base + k;
+    if (i >= 0 && i < n) return i;
+    if (wall) return -1;
+    i %= n;
+    return i < 0 ? i + n : i;
 }
 
 struct NodeArrays {
