@@ -398,15 +398,18 @@ __global__ __launch_bounds__(kBlock) void k_lb(const DropDev* __restrict__ drops
     // The band flag of this cell's strip is requested before the
     // populations: loads return in order, so waiting for the flag then does
     // not wait for the populations, and a band wavefront's F loads overlap
-    // them instead of following them.  A lone 2D droplet's kernel
-    // in fp32 requests it after them: few of its wavefronts lie in the band, and the others
-    // then do not start on a line that the node kernel wrote just before
-    // (1024x512: 13.8 against 15.4 us per coupled step; the 256-droplet fp16
-    // batch 246 against 236 us).
+    // them instead of following them.  A lone 2D droplet's kernel in fp32 with
+    // non-temporal stores requests it after them: its populations come from
+    // beyond L2, and the wavefronts outside the band then do not start on a
+    // line that the node kernel wrote just before (us per coupled step, early /
+    // late: 512x512 10.9 / 10.5, 1024x512 16.8 / 15.4, 1280x640 19.4 / 18.8, but
+    // 2048x1024 36.3 / 37.4).  With plain stores late is slower everywhere
+    // (1024x512 13.9 / 14.1, 1024x768 15.8 / 16.6, 2048x1024 30.7 / 31.5), as in
+    // the 256-droplet fp16 batch (236 / 246).
     // A tiled wavefront reads its strips' flags as one aligned word.
     using SW = typename Strip<DIM, S>::Word;
     constexpr int SPW = Strip<DIM, S>::per64;
-    constexpr bool LATE = DIM == 2 && ONE && S == ST_F32;
+    constexpr bool LATE = DIM == 2 && ONE && S == ST_F32 && NT;
     const long long fi = D.flag_off + (long long)(z * ny + y) * D.nstrip + (x >> Strip<DIM, S>::shift);
     int flag;
     auto get_flag = [&](bool given) {
