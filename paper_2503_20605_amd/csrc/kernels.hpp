@@ -1379,8 +1379,16 @@ __global__ __launch_bounds__(kBlock) void k_force3(const DropDev* __restrict__ d
 // would grow beyond a budget).  Their 64 taps each overlap heavily,
 // so the contributions are first summed in an LDS box that covers the
 // chunk's taps, and each touched cell then takes one global atomic add per
-// component instead of one per contribution.  A chunk whose box exceeds
-// kBoxCells (vertices far apart) adds straight to global memory.
+// component instead of one per contribution.  The chunks are cut when an
+// interface is set; where it has been stretched since, and a chunk's box
+// exceeds kBoxCells, the chunk is taken in runs of kRun vertices with a box
+// each, one after the other, and only a run whose own box is too large adds
+// straight to global memory.  336x336x112, 64 002 vertices, a drop spreading
+// from a hemisphere, us per coupled step at the start / after 5 000 / after
+// 20 000 steps: 570 / 586 / 597 with chunks that added straight to memory,
+// 571 / 575 / 576 with runs of 16, 571 / 582 / 583 with 8, 571 / 577 / 582 with
+// 32.  The loop over the runs takes registers: without the bound on them a
+// compute unit holds one workgroup (80x80x60: 37.9 against 34.3 us per step).
 // What bounds it: the adds to global memory (more than half of the time with
 // chunks of 16 vertices on 256 lanes), so chunks are as large as one
 // workgroup of 16 wavefronts takes in four rounds.  Kernel time on 80x80x60
@@ -1400,10 +1408,12 @@ __global__ __launch_bounds__(kBlock) void k_force3(const DropDev* __restrict__ d
 #endif
 constexpr int kChunk = IBLB_SPREAD_CHUNK;
 constexpr int kBoxCells = IBLB_SPREAD_BOX;
+constexpr int kRun = 16;         // vertices of a run of a chunk that has outgrown the box
+constexpr int kSpreadWaves = 8;  // wavefronts per SIMD: two workgroups on a compute unit
 constexpr int kSpreadBlock = IBLB_SPREAD_BLOCK;  // wavefronts each taking every (block / 64)-th vertex
 static_assert(3 * kChunk <= kSpreadBlock, "a lane per vertex and axis");
 
-__global__ __launch_bounds__(kSpreadBlock) void k_spread3(const DropDev* __restrict__ drops, NodeArrays A,
+__global__ __launch_bounds__(kSpreadBlock, kSpreadWaves) void k_spread3(const DropDev* __restrict__ drops, NodeArrays A,
                                                     const int4* __restrict__ chunks,
                                                     unsigned long long* __restrict__ Fq_all,
                                                     uint8_t* __restrict__ flags_all,
@@ -1465,85 +1475,109 @@ __global__ __launch_bounds__(kSpreadBlock) void k_spread3(const DropDev* __restr
     __syncthreads();
     // without a finite vertex there is no box; each extent (up to 2^25 + 4) is
     // checked by itself, for their product need not fit 64 bits
-    const bool any = lo[0] <= hi[0];
-    const int ex = any ? hi[0] - lo[0] + 4 : 0, ey = any ? hi[1] - lo[1] + 4 : 0, ez = any ? hi[2] - lo[2] + 4 : 0;
-    const bool fits = any && ex <= kBoxCells && ey <= kBoxCells && ez <= kBoxCells &&
-                      (long long)ex * ey * ez <= kBoxCells;
-    const int ncb = fits ? ex * ey * ez : 0;
-    for (int c = t; c < ncb; c += kSpreadBlock) {
-        box[c] = 0;
-        box[kBoxCells + c] = 0;
-        box[2 * kBoxCells + c] = 0;
-        touched[c] = 0;
-    }
-    __syncthreads();
+    int ex, ey, ez;
+    bool fits;
+    auto measure = [&]() {
+        const bool any = lo[0] <= hi[0];
+        ex = any ? hi[0] - lo[0] + 4 : 0;
+        ey = any ? hi[1] - lo[1] + 4 : 0;
+        ez = any ? hi[2] - lo[2] + 4 : 0;
+        fits = any && ex <= kBoxCells && ey <= kBoxCells && ez <= kBoxCells && (long long)ex * ey * ez <= kBoxCells;
+        return fits || !any;
+    };
+    const int run = measure() ? kChunk : kRun;
     unsigned long long* __restrict__ Fq = Fq_all + 3LL * D.c_off;
     bool fine = true;
     const int k = t & 63;  // tap of this lane; one vertex per wavefront at a time
     const int kx = k & 3, ky = (k >> 2) & 3, kz = k >> 4;
-    const int ktap = fits ? (kz * ey + ky) * ex + kx : 0;  // its place in the box
-    for (int v = t >> 6; v < count; v += kSpreadBlock / 64) {
-        if (!sok[v]) continue;  // the same for the whole wavefront
-        const float w = swt[v][0][kx] * swt[v][1][ky] * swt[v][2][kz];
-        const int gx = scell[v][0][kx], gy = scell[v][1][ky], gz = scell[v][2][kz];
-        float lost[3] = {0.f, 0.f, 0.f};
-        if ((gx | gy | gz) < 0) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) lost[a] = sph[v][a] * w;
-        } else if (fits) {
-            const int c = ((sbase[v][2] - lo[2]) * ey + (sbase[v][1] - lo[1])) * ex + (sbase[v][0] - lo[0]) + ktap;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const float val = sph[v][a] * w;
-                if (fq_ok(val))
-                    atomicAdd(&box[a * kBoxCells + c], fq_of(val));
-                else
-                    fine = false;
+    for (int first = 0; first < count; first += run) {
+        const int last = first + run < count ? first + run : count;
+        if (run < kChunk) {  // the run's own box
+            __syncthreads();
+            if (t < 3) {
+                lo[t] = INT_MAX;
+                hi[t] = INT_MIN;
             }
-            touched[c] = 1;
-        } else {
+            __syncthreads();
+            if (v0 < last - first && sok[first + v0]) {
+                atomicMin(&lo[a0], sbase[first + v0][a0]);
+                atomicMax(&hi[a0], sbase[first + v0][a0]);
+            }
+            __syncthreads();
+            measure();
+        }
+        const int ncb = fits ? ex * ey * ez : 0;
+        for (int c = t; c < ncb; c += kSpreadBlock) {
+            box[c] = 0;
+            box[kBoxCells + c] = 0;
+            box[2 * kBoxCells + c] = 0;
+            touched[c] = 0;
+        }
+        __syncthreads();
+        const int ktap = fits ? (kz * ey + ky) * ex + kx : 0;  // its place in the box
+        for (int v = first + (t >> 6); v < last; v += kSpreadBlock / 64) {
+            if (!sok[v]) continue;  // the same for the whole wavefront
+            const float w = swt[v][0][kx] * swt[v][1][ky] * swt[v][2][kz];
+            const int gx = scell[v][0][kx], gy = scell[v][1][ky], gz = scell[v][2][kz];
+            float lost[3] = {0.f, 0.f, 0.f};
+            if ((gx | gy | gz) < 0) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) lost[a] = sph[v][a] * w;
+            } else if (fits) {
+                const int c = ((sbase[v][2] - lo[2]) * ey + (sbase[v][1] - lo[1])) * ex + (sbase[v][0] - lo[0]) + ktap;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const float val = sph[v][a] * w;
+                    if (fq_ok(val))
+                        atomicAdd(&box[a * kBoxCells + c], fq_of(val));
+                    else
+                        fine = false;
+                }
+                touched[c] = 1;
+            } else {
+                const int row = gz * D.ny + gy, cell = row * D.nx + gx;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const float val = sph[v][a] * w;
+                    if (fq_ok(val))
+                        atomicAdd(Fq + a * D.ncell + cell, fq_of(val));
+                    else
+                        fine = false;
+                }
+                flags_all[D.flag_off + row * D.nstrip + (gx >> D.sshift)] = 1;
+            }
+            if (want_dropped) {
+#pragma unroll
+                for (int a = 0; a < 3; ++a) lost[a] = group_sum<64>(lost[a]);
+                if (k == 0) {
+                    const int j = A.perm[ch.y + v];
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) A.dropped[a * st + j] = lost[a];
+                }
+            }
+        }
+        if (!fits) continue;
+        __syncthreads();
+        // c / ex and (c / ex) / ey of c < kBoxCells by the reciprocal: exact, the
+        // half keeps the product 2^-11 away from a whole number at least
+        const float rx = 1.f / (float)ex, ry = 1.f / (float)ey;
+        for (int c = t; c < ncb; c += kSpreadBlock) {
+            if (!touched[c]) continue;
+            const int r = (int)(((float)c + 0.5f) * rx), cz = (int)(((float)r + 0.5f) * ry);
+            const int cx = c - r * ex, cy = r - cz * ey;
+            // a touched cell received a fluid tap, so none of these is -1
+            const int gx = tap_index(lo[0], cx, D.nx, D.bcx), gy = tap_index(lo[1], cy, D.ny, D.bcy),
+                      gz = tap_index(lo[2], cz, D.nz, D.bcz);
             const int row = gz * D.ny + gy, cell = row * D.nx + gx;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
-                const float val = sph[v][a] * w;
-                if (fq_ok(val))
-                    atomicAdd(Fq + a * D.ncell + cell, fq_of(val));
-                else
-                    fine = false;
+                const unsigned long long v = box[a * kBoxCells + c];
+                if (v != 0) atomicAdd(Fq + a * D.ncell + cell, v);
             }
             flags_all[D.flag_off + row * D.nstrip + (gx >> D.sshift)] = 1;
         }
-        if (want_dropped) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) lost[a] = group_sum<64>(lost[a]);
-            if (k == 0) {
-                const int j = A.perm[ch.y + v];
-#pragma unroll
-                for (int a = 0; a < 3; ++a) A.dropped[a * st + j] = lost[a];
-            }
-        }
     }
     if (!fine) atomicOr(status + ch.x, 2);
-    if (!fits) return;
-    __syncthreads();
-    // c / ex and (c / ex) / ey of c < kBoxCells by the reciprocal: exact, the
-    // half keeps the product 2^-11 away from a whole number at least
-    const float rx = 1.f / (float)ex, ry = 1.f / (float)ey;
-    for (int c = t; c < ncb; c += kSpreadBlock) {
-        if (!touched[c]) continue;
-        const int r = (int)(((float)c + 0.5f) * rx), cz = (int)(((float)r + 0.5f) * ry);
-        const int cx = c - r * ex, cy = r - cz * ey;
-        // a touched cell received a fluid tap, so none of these is -1
-        const int gx = tap_index(lo[0], cx, D.nx, D.bcx), gy = tap_index(lo[1], cy, D.ny, D.bcy),
-                  gz = tap_index(lo[2], cz, D.nz, D.bcz);
-        const int row = gz * D.ny + gy, cell = row * D.nx + gx;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const unsigned long long v = box[a * kBoxCells + c];
-            if (v != 0) atomicAdd(Fq + a * D.ncell + cell, v);
-        }
-        flags_all[D.flag_off + row * D.nstrip + (gx >> D.sshift)] = 1;
-    }
 }
 
 // ---------------------------------------------------------------------------
