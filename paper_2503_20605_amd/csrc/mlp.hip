@@ -40,16 +40,41 @@ struct MlpLayout {
     std::vector<long long> woff, boff;  // offsets in the packed parameter vector
     long long P = 0;
     size_t master, grad, m, v, wb, partial, total;
-    // layer by layer (wider networks): the input (bf16), the output-side
-    // gradients (bf16) of two consecutive layers, used in turn, and
+    // layer by layer (wider networks; training passes below rows_from): the
+    // input (bf16), the output-side gradients (bf16) of two consecutive
+    // layers, used in turn, and
     size_t xb = 0, dZb[2] = {0, 0};
     std::vector<size_t> Z, H;  // Z[l]: layer l output (fp32); H[l]: layer l input (bf16)
     // whole passes in one launch (k_mlp_rows) for narrow networks: the packed
     // weights, and what a training pass keeps
     bool rows = false;
+    int rows_from = 1;  // batch from which on training passes are
     size_t packed = 0, zbuf = 0, tbuf = 0;
     MlpRows R;
 };
+
+// Batch from which on a narrow network's training pass runs in one launch
+// (k_mlp_rows).  That saves the launches of the layers, and the outputs and
+// their gradients do not travel through memory; but one workgroup takes its 32
+// rows through all output columns, 256 at a time, where the products layer by
+// layer spread the columns over the device.  In microseconds: 15 a layer
+// (nothing with a single one) and 4.5e-6 per row and column saved, per column
+// 0.003 (last layer's input up to 64 wide) to 0.008 (256 wide) spent, 0.010
+// with a single layer, 1.4 times that where the packed weights (4 N K bytes)
+// exceed the 32 MiB of the L2 caches.  Over 852 points of 1 to 4096 rows,
+// 1280 to 65536 columns, 1 to 9 layers the way so chosen is at most 10 % off
+// the faster one, 0.8 % in the root mean square.  One launch against layers,
+// us per training step: 4-256-256-256-1280, 1 row 84 / 138, 4096 rows 107 /
+// 244; -8192, 1 row 218 / 208, 1024 rows 251 / 375; -65536, 32 rows 1803 / 823;
+// 16-8192, 32 rows 127 / 48.  (The weights stay packed for the forward passes:
+// 35 us a step for 256-65536, little for smaller ones.)
+int rows_from(int L, const int* w) {
+    const double N = w[L], K = w[L - 1], packed = 4.0 * N * K;
+    double column = L == 1 ? 0.010 : 0.003 + 0.005 * std::min(1.0, std::max(0.0, (K - 64) / 192));
+    if (packed > 32 << 20) column *= 1.4;
+    const double saved = L == 1 ? 0.0 : 15.0 * L;
+    return std::max(1, (int)std::ceil((column - saved / N) / 4.5e-6));
+}
 
 bool mlp_plan(int L, const int* widths, int B, MlpLayout& Y, std::string& err) {
     if (L < 1 || L > 16 || !widths) { err = "n_layers must be 1..16 with widths given"; return false; }
@@ -80,15 +105,17 @@ bool mlp_plan(int L, const int* widths, int B, MlpLayout& Y, std::string& err) {
     Y.wb = take(2 * Y.P);
     Y.rows = true;
     for (int l = 0; l < L; ++l) Y.rows = Y.rows && Y.w[l] <= kRowsWidth;
-    if (!Y.rows) {
+    if (Y.rows) Y.rows_from = rows_from(L, Y.w.data());
+    const unsigned long long BL = Y.rows ? std::min(B, Y.rows_from - 1) : B;  // rows that go layer by layer
+    if (BL > 0) {
         Y.Z.resize(L);
         Y.H.resize(L);
         for (int l = 0; l < L; ++l) {
-            Y.Z[l] = take(4ull * B * Y.w[l + 1]);
-            Y.H[l] = take(2ull * B * Y.w[l]);
+            Y.Z[l] = take(4 * BL * Y.w[l + 1]);
+            Y.H[l] = take(2 * BL * Y.w[l]);
         }
         Y.xb = Y.H[0];
-        for (int h = 0; h < 2; ++h) Y.dZb[h] = take(2ull * B * Y.maxw);
+        for (int h = 0; h < 2; ++h) Y.dZb[h] = take(2 * BL * Y.maxw);
     }
     Y.partial = take(8ull * std::max(mlp_cdiv(Y.w[L], 64) * mlp_cdiv(B, kColsumRows), mlp_cdiv(B, kRows)));
     if (Y.rows) {
@@ -97,19 +124,20 @@ bool mlp_plan(int L, const int* widths, int B, MlpLayout& Y, std::string& err) {
         R.batch = 0;
         R.ld = mlp_cdiv(B, kRows) * kRows;
         long long pk = 0, z = 0, t = 0;
+        const bool trains = Y.rows_from <= B;  // else forward passes only
         for (int l = 0; l <= L; ++l) R.w[l] = Y.w[l];
         for (int l = 0; l < L; ++l) {
             R.boff[l] = Y.boff[l];
             R.wp[l] = pk;
             pk += 8 * packed_pieces(Y.w[l], Y.w[l + 1]);
             R.wt[l] = pk;
-            pk += 8 * packed_pieces(Y.w[l + 1], Y.w[l]);
+            if (trains) pk += 8 * packed_pieces(Y.w[l + 1], Y.w[l]);
             R.z[l] = z;
-            if (l < L - 1) z += R.ld * kRowsWidth;
+            if (trains && l < L - 1) z += R.ld * kRowsWidth;
             R.ht[l] = t;
-            t += R.ld * Y.w[l];
+            if (trains || l == 0) t += R.ld * Y.w[l];
             R.dt[l] = t;
-            t += R.ld * Y.w[l + 1];
+            if (trains) t += R.ld * Y.w[l + 1];
         }
         Y.packed = take(2ull * pk);
         Y.zbuf = take(4ull * z);
@@ -209,19 +237,28 @@ void gemm(const iblb_mlp* c, const Operand& A, const Operand& B, float* Cf, uint
     launch_gemm<KP>(c, grid, A, B, Cf, Hb, ldc, bias, Zpre, colsum, M, N, K, act, kc, avec, bvec);
 }
 
-// The packed copies of the weights, from the bf16 one.
-void pack_weights(const iblb_mlp* c) {
-    const MlpLayout& Y = c->Y;
-    if (!Y.rows) return;
+// Where the packed copies of the weights lie (narrow networks).
+MlpPack pack_layout(const MlpLayout& Y) {
     MlpPack P;
-    long long most = 0;
+    P.L = Y.L;
+    P.both = Y.rows_from <= Y.B;
     for (int l = 0; l <= Y.L; ++l) P.w[l] = Y.w[l];
     for (int l = 0; l < Y.L; ++l) {
         P.woff[l] = Y.woff[l];
         P.wp[l] = Y.R.wp[l];
         P.wt[l] = Y.R.wt[l];
-        most = std::max(most, packed_pieces(Y.w[l], Y.w[l + 1]) + packed_pieces(Y.w[l + 1], Y.w[l]));
     }
+    return P;
+}
+
+// The packed copies of the weights, from the bf16 one.
+void pack_weights(const iblb_mlp* c) {
+    const MlpLayout& Y = c->Y;
+    if (!Y.rows) return;
+    const MlpPack P = pack_layout(Y);
+    long long most = 0;
+    for (int l = 0; l < Y.L; ++l)
+        most = std::max(most, packed_pieces(Y.w[l], Y.w[l + 1]) + packed_pieces(Y.w[l + 1], Y.w[l]));
     hipLaunchKernelGGL(k_pack, dim3((unsigned)mlp_cdiv(most, kMlpBlock), (unsigned)Y.L), dim3(kMlpBlock), 0, c->stream,
                        P, (const uint16_t*)c->at<uint16_t>(Y.wb), c->at<uint16_t>(Y.packed));
 }
@@ -488,13 +525,14 @@ int iblb_mlp_gradients(iblb_mlp* c, const float* d_x, const float* d_t, int batc
     const int L = Y.L;
     const long long ny = (long long)batch * Y.w[L];
     const dim3 lgrid((unsigned)mlp_cdiv(Y.w[L], 64), (unsigned)mlp_cdiv(batch, kColsumRows));
-    const int nblk = Y.rows ? (int)mlp_cdiv(batch, kRows) : (int)(lgrid.x * lgrid.y);
+    const bool rows = Y.rows && batch >= Y.rows_from;
+    const int nblk = rows ? (int)mlp_cdiv(batch, kRows) : (int)(lgrid.x * lgrid.y);
     float* grad = c->at<float>(Y.grad);
-    if (!Y.rows && (rc = mlp_forward(c, d_x, batch))) return rc;
+    if (!rows && (rc = mlp_forward(c, d_x, batch))) return rc;
     // the gradients of every layer are accumulated atomically: zeroed first
     hipLaunchKernelGGL(k_zero_f32, dim3((unsigned)mlp_cdiv(Y.P, kMlpBlock)), dim3(kMlpBlock), 0, c->stream, grad,
                        Y.P);
-    if (Y.rows) {
+    if (rows) {
         rows_gradients(c, d_x, d_t, batch, nblk);
     } else {
         // dZ of layer l lives in buffer (L - 1 - l) % 2; the loss gradient also
@@ -546,10 +584,10 @@ int iblb_mlp_adam_step(iblb_mlp* c, float lr, float beta1, float beta2, float ep
     const MlpLayout& Y = c->Y;
     c->t += 1;
     const float bc1 = 1.f - powf(beta1, (float)c->t), bc2 = 1.f - powf(beta2, (float)c->t);
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)mlp_cdiv(Y.P, kMlpBlock)), dim3(kMlpBlock), 0, c->stream,
-                       c->at<float>(Y.master), c->at<uint16_t>(Y.wb), (const float*)c->at<float>(Y.grad),
-                       c->at<float>(Y.m), c->at<float>(Y.v), Y.P, lr, beta1, beta2, eps, bc1, bc2);
-    pack_weights(c);
+    hipLaunchKernelGGL(Y.rows ? k_adam<true> : k_adam<false>, dim3((unsigned)mlp_cdiv(Y.P, kMlpBlock)),
+                       dim3(kMlpBlock), 0, c->stream, c->at<float>(Y.master), c->at<uint16_t>(Y.wb),
+                       (const float*)c->at<float>(Y.grad), c->at<float>(Y.m), c->at<float>(Y.v), Y.P, lr, beta1, beta2,
+                       eps, bc1, bc2, Y.rows ? pack_layout(Y) : MlpPack{}, c->at<uint16_t>(Y.packed));
     MLPCHK(c, hipGetLastError());
     return IBLB_OK;
 }

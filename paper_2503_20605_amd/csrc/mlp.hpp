@@ -15,7 +15,8 @@
 //   k_mlp_rows      a narrow network's whole forward (or forward and backward)
 //                   pass, 32 rows of the batch per workgroup
 //   k_wgrad         the weight gradients of all its layers
-//   k_pack          its weights in the order of the matrix instruction
+//   k_pack          its weights in the order of the matrix instruction (when they
+//                   are set; k_adam keeps them so)
 //   k_mse_colsum    loss, dY = 2 (Y - T) / (B n) and the last layer's bias
 //                   gradient (column sums of dY): 64 columns x 256 rows
 //                   per workgroup, reduced in LDS, then added atomically
@@ -555,10 +556,11 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const X* __r
     }
 }
 
-// The weights of every layer packed for Pieces, both ways, from the
-// bf16 copy wb (row-major [w[l]][w[l + 1]] at woff): one lane per 16-byte
+// The weights of every layer packed for Pieces, both ways (both; else for
+// forward passes only), from the bf16 copy wb (row-major [w[l]][w[l + 1]] at woff): one lane per 16-byte
 // piece, layer blockIdx.y.
 struct MlpPack {
+    int L, both;
     int w[kMaxLayers + 1];
     long long woff[kMaxLayers], wp[kMaxLayers], wt[kMaxLayers];
 };
@@ -566,7 +568,7 @@ __global__ __launch_bounds__(kMlpBlock) void k_pack(MlpPack P, const uint16_t* _
                                                     uint16_t* __restrict__ packed) {
     const int l = blockIdx.y, in = P.w[l], out = P.w[l + 1];
     const uint16_t* __restrict__ W = wb + P.woff[l];
-    const long long nf = packed_pieces(in, out), nt = packed_pieces(out, in);
+    const long long nf = packed_pieces(in, out), nt = P.both ? packed_pieces(out, in) : 0;
     for (long long v = (long long)blockIdx.x * kMlpBlock + threadIdx.x; v < nf + nt;
          v += (long long)gridDim.x * kMlpBlock) {
         const bool tr = v >= nf;  // transposed: B(k, j) = W[j][k]
@@ -585,6 +587,21 @@ __global__ __launch_bounds__(kMlpBlock) void k_pack(MlpPack P, const uint16_t* _
     }
 }
 
+// The packed copies of parameter i, h its bf16 value (biases have none).
+__device__ __forceinline__ void put_packed(const MlpPack& P, uint16_t* __restrict__ packed, long long i, uint16_t h) {
+    int l = 0;
+    while (l + 1 < P.L && i >= P.woff[l + 1]) ++l;
+    const unsigned in = P.w[l], out = P.w[l + 1];
+    const long long o = i - P.woff[l];
+    if (o >= (long long)in * out) return;
+    const unsigned k = (unsigned)o / out, j = (unsigned)o - k * out;  // (in <= kRowsWidth: 32 bits)
+    auto at = [](unsigned r, unsigned c, unsigned NT) {  // element B(r, c) of a packed operand
+        return ((long long)(r / 16 * NT + c / 32) * 64 + (c & 31) + 32 * (r / 8 & 1)) * 8 + (r & 7);
+    };
+    packed[P.wp[l] + at(k, j, (out + 31) / 32)] = h;
+    if (P.both) packed[P.wt[l] + at(j, k, (in + 31) / 32)] = h;
+}
+
 // x[i] = 0 for i < n
 __global__ void k_zero_f32(float* __restrict__ x, long long n) {
     const long long i = (long long)blockIdx.x * kMlpBlock + threadIdx.x;
@@ -592,10 +609,14 @@ __global__ void k_zero_f32(float* __restrict__ x, long long n) {
 }
 
 // Adam (Kingma & Ba) on the fp32 master copy; bc1 = 1 - beta1^t,
-// bc2 = 1 - beta2^t.  Writes the bf16 copy used by the products.
+// bc2 = 1 - beta2^t.  Writes the bf16 copy used by the products and, with
+// PACK, its packed form (element by element: a launch of k_pack after every
+// step took 20 us).
+template <bool PACK>
 __global__ void k_adam(float* __restrict__ w, uint16_t* __restrict__ wb, const float* __restrict__ g,
                        float* __restrict__ m, float* __restrict__ v, long long n, float lr,
-                       float beta1, float beta2, float eps, float bc1, float bc2) {
+                       float beta1, float beta2, float eps, float bc1, float bc2, MlpPack K,
+                       uint16_t* __restrict__ packed) {
     const long long i = (long long)blockIdx.x * kMlpBlock + threadIdx.x;
     if (i >= n) return;
     const float gi = g[i];
@@ -605,7 +626,9 @@ __global__ void k_adam(float* __restrict__ w, uint16_t* __restrict__ wb, const f
     v[i] = vi;
     const float wi = w[i] - lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
     w[i] = wi;
-    wb[i] = to_bf16(wi);
+    const uint16_t h = to_bf16(wi);
+    wb[i] = h;
+    if (PACK) put_packed(K, packed, i, h);
 }
 
 // fp32 -> bf16 (nearest even), n elements

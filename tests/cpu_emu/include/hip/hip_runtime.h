@@ -159,8 +159,20 @@ inline void launch(void* stream, dim3 g, dim3 b, K k, A... a) {
 #define blockDim (::hipemu::block_dim())
 #define gridDim (::hipemu::grid_dim())
 
+// With EMU_LAUNCHES=<file> in the environment, the text of every launch's
+// kernel expression is appended to that file.
+namespace hipemu {
+inline void note_launch(const char* kern) {
+    static FILE* f = getenv("EMU_LAUNCHES") ? fopen(getenv("EMU_LAUNCHES"), "a") : nullptr;
+    if (f) {
+        fprintf(f, "%s\n", kern);
+        fflush(f);
+    }
+}
+}  // namespace hipemu
+
 #define hipLaunchKernelGGL(kern, grid, block, shmem, stream, ...) \
-    ::hipemu::launch((void*)(stream), dim3(grid), dim3(block), kern, __VA_ARGS__)
+    (::hipemu::note_launch(#kern), ::hipemu::launch((void*)(stream), dim3(grid), dim3(block), kern, __VA_ARGS__))
 
 // launch with start/stop events stamped by the dispatch (timing is faked)
 template <typename K, typename Ev, typename... A>

@@ -34,7 +34,7 @@ def run_cases(jobs):
 def run_case(params_list, nodes_list=None, tris_list=None, steps=(1,), storage=0,
              graph_steps=None, shape=None, f0dev=None, forces=None, timing=False,
              inactive=(), rest=None, timeout=600, direct_chunks=False, masks=False,
-             contact=None):
+             contact=None, launches=None):
     import build as emu_build
     from paper_2503_20605_amd._lib import iblb_diag
     with _build_lock:
@@ -100,7 +100,11 @@ def run_case(params_list, nodes_list=None, tris_list=None, steps=(1,), storage=0
         # locals
         env["ASAN_OPTIONS"] = "detect_leaks=0:abort_on_error=0:halt_on_error=1:detect_stack_use_after_return=0"
         env["UBSAN_OPTIONS"] = "print_stacktrace=1:halt_on_error=1"
+        if launches is not None:
+            env["EMU_LAUNCHES"] = os.path.join(d, "launches.txt")
         r = subprocess.run([exe, d], capture_output=True, text=True, timeout=timeout, env=env)
+        if launches is not None and os.path.exists(env["EMU_LAUNCHES"]):
+            launches += open(env["EMU_LAUNCHES"]).read().split("\n")
         if r.returncode != 0:
             raise RuntimeError(f"emulated run failed (rc={r.returncode}):\n{r.stderr[-6000:]}")
         status = open(os.path.join(d, "status.txt")).read().split("\n", 1)
@@ -141,11 +145,12 @@ def run_case(params_list, nodes_list=None, tris_list=None, steps=(1,), storage=0
         return outs
 
 
-def run_mlp(widths, params, x, t, lr=1e-3, timeout=600, overlap=None):
+def run_mlp(widths, params, x, t, lr=1e-3, timeout=600, overlap=None, launches=None):
     """One forward, one gradient evaluation and one Adam step of the network
     kernels in the sanitizer build.  Returns (y, grads, loss, params_after);
     with overlap = (offset of x, offset of y), floats into one buffer, also
-    the outputs of the two forward calls on it."""
+    the outputs of the two forward calls on it.  launches: a list that the
+    kernel expressions of the launches are appended to (also run_case)."""
     import build as emu_build
     exe = emu_build.build()
     with tempfile.TemporaryDirectory() as d:
@@ -159,7 +164,11 @@ def run_mlp(widths, params, x, t, lr=1e-3, timeout=600, overlap=None):
         env = dict(os.environ)
         env["ASAN_OPTIONS"] = "detect_leaks=0:halt_on_error=1:detect_stack_use_after_return=0"
         env["UBSAN_OPTIONS"] = "print_stacktrace=1:halt_on_error=1"
+        if launches is not None:
+            env["EMU_LAUNCHES"] = os.path.join(d, "launches.txt")
         r = subprocess.run([exe, d], capture_output=True, text=True, timeout=timeout, env=env)
+        if launches is not None:
+            launches += open(env["EMU_LAUNCHES"]).read().split("\n")
         if r.returncode != 0:
             raise RuntimeError(f"emulated network run failed (rc={r.returncode}):\n{r.stderr[-6000:]}")
         y = np.fromfile(os.path.join(d, "y.bin"), dtype=np.float32).reshape(B, widths[-1])

@@ -1,0 +1,77 @@
+"""Which kernels the rules of the dispatch pick at both sides of their lines, in
+the sanitizer build, and what they give against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import mlp as ref
+
+
+def _check_network(widths, batch, y, g, loss, x, t, p):
+    # bf16 operands, fp32 sums: the tolerances of the other network tests
+    yo, _ = ref.forward(p, widths, x)
+    lo, go = ref.loss_and_grad(p, widths, x, t)
+    assert np.max(np.abs(y - yo)) <= 3e-2 * np.max(np.abs(yo))
+    assert abs(loss - lo) <= 2e-2 * lo
+    cos = float(np.dot(g, go) / (np.linalg.norm(g) * np.linalg.norm(go)))
+    assert cos >= 0.999 and np.linalg.norm(g - go) <= 2e-2 * np.linalg.norm(go)
+
+
+def _network(widths, batch):
+    rng = np.random.default_rng(5)
+    return (ref.init_params(widths, 7), rng.uniform(-1, 1, (batch, widths[0])),
+            0.3 * rng.standard_normal((batch, widths[-1])))
+
+
+# narrow networks: many outputs for few rows, and a single layer, train layer
+# by layer; the others in one launch
+TRAINING = [([16, 24], 5, False), ([4, 24, 12000], 3, False), ([4, 24, 8000], 3, True), ([4, 16, 16, 70], 33, True),
+            ([4, 300, 20], 3, False)]
+
+
+@pytest.mark.parametrize("widths,batch,one", TRAINING)
+def test_training_pass(widths, batch, one):
+    from emu import run_mlp
+    p, x, t = _network(widths, batch)
+    launches = []
+    y, g, loss, _ = run_mlp(widths, p, x, t, launches=launches)
+    assert any("k_mlp_rows<1" in k for k in launches) == one
+    assert any("k_mse_colsum" in k for k in launches) != one
+    # the packed weights come with the update: set once, not packed again
+    assert sum("k_pack" in k for k in launches) == (max(widths[:-1]) <= 256)
+    _check_network(widths, batch, y, g, loss, x, t, p)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("widths,batch", [([4, 100, 33, 70], 40), ([256, 256, 1000], 33), ([20, 16384], 5), ([1, 1], 1)])
+def test_updated_weights_are_the_ones_that_are_used(widths, batch):
+    """After training steps the forward pass equals that of a network that was
+    given the same weights, bit for bit."""
+    from paper_2503_20605_amd import MLP
+    p, x, t = _network(widths, batch)
+    print("[rules] packed weights", widths, batch, flush=True)
+    a, b = MLP(widths, batch), MLP(widths, batch)
+    a.set_params(p)
+    for _ in range(3):
+        a.train_step(x, t, 1e-2)
+    b.set_params(a.get_params())
+    assert np.array_equal(a.forward(x).cpu().numpy(), b.forward(x).cpu().numpy())
+    la, ga = a.gradients(x, t)
+    lb, gb = b.gradients(x, t)
+    assert la == lb and np.max(np.abs(ga - gb)) <= 1e-5 * np.max(np.abs(gb))  # (atomics: the order of the sums)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("widths,max_batch,batches", [([4, 64, 256, 16384], 1024, (1, 33, 512, 1024)),
+                                                      ([16, 2000], 2400, (7, 2400)), ([200, 20], 64, (64,))])
+def test_training_passes_of_one_network(widths, max_batch, batches):
+    """Batches at both sides of the line on one handle, in turn."""
+    from paper_2503_20605_amd import MLP
+    p, _, _ = _network(widths, 1)
+    m = MLP(widths, max_batch)
+    m.set_params(p)
+    for b in batches + batches[:1]:
+        print("[rules] training", widths, b, flush=True)
+        _, x, t = _network(widths, b)
+        y = m.forward(x).cpu().numpy()
+        loss, g = m.gradients(x, t)
+        _check_network(widths, b, y, g, loss, x, t, p)
