@@ -133,7 +133,7 @@ bool mlp_plan(int L, const int* widths, int B, MlpLayout& Y, std::string& err) {
             R.wt[l] = pk;
             if (trains) pk += 8 * packed_pieces(Y.w[l + 1], Y.w[l]);
             R.z[l] = z;
-            if (trains && l < L - 1) z += R.ld * kRowsWidth;
+            if (trains && l < L - 1) z += R.ld * mlp_cdiv(Y.w[l + 1], 32) * 32;
             R.ht[l] = t;
             if (trains || l == 0) t += R.ld * Y.w[l];
             R.dt[l] = t;

@@ -314,7 +314,8 @@ struct MlpRows {
     long long boff[kMaxLayers];  // biases in the parameter vector
     // training
     long long ld;                // row length of the transposed operands below: batch rounded up to 32
-    long long z[kMaxLayers];     // pre-activations of layer l (floats), in the lanes' own order
+    long long z[kMaxLayers];     // pre-activations of layer l (floats), in the lanes' own order: per workgroup
+                                 // 1024 for each 32x32 tile
     long long ht[kMaxLayers];    // input of layer l, transposed: [w[l]][ld] bf16
     long long dt[kMaxLayers];    // gradient at the output of layer l, transposed: [w[l + 1]][ld] bf16
 };
@@ -429,8 +430,8 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const X* __r
     f32x16 zero;
 #pragma unroll
     for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-    float* __restrict__ zw =
-        TRAIN ? zbuf + ((long long)blockIdx.x * (kRowsWidth / 32) + wave) * 16 * 64 + lane : nullptr;
+    // this wavefront's tile of a hidden layer's pre-activations
+    auto zw = [&](int l) { return zbuf + P.z[l] + ((long long)blockIdx.x * n_tiles(P.w[l + 1]) + wave) * 1024 + lane; };
     int cur = 0;
     for (int l = 0; l < L - 1; ++l) {
         const int Nl = P.w[l + 1];
@@ -445,7 +446,7 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const X* __r
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const float z = acc[r] + bj;
-                if (TRAIN) zw[P.z[l] + r * 64] = z;
+                if (TRAIN) zw(l)[r * 64] = z;
                 const bool in = j < Nl && (!TRAIN || row0 + result_row(r, lane) < M);
                 const uint16_t v = to_bf16(gelu(z));
                 h[r] = in ? v : (uint16_t)0;
@@ -525,7 +526,7 @@ __global__ __launch_bounds__(kRowsBlock) void k_mlp_rows(MlpRows P, const X* __r
         float z[16];
         if (mine)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) z[r] = zw[P.z[l] + r * 64];
+            for (int r = 0; r < 16; ++r) z[r] = zw(l)[r * 64];
         if (l > 0 && wave < Tl) B.load(bwd(l), k_steps(Nl), 0, wave, Tl, lane);
         __syncthreads();  // every wavefront is done with the operand below
         if (mine) {

@@ -41,6 +41,20 @@ def test_training_pass(widths, batch, one):
     _check_network(widths, batch, y, g, loss, x, t, p)
 
 
+@pytest.mark.parametrize("widths", [[4, 8, 8, 2], [4, 32, 32, 32, 40], [4, 64, 64, 100]])
+def test_workspace_of_narrow_layers(widths):
+    """A row of the batch takes what a training pass keeps of it: per hidden
+    layer the pre-activations (fp32, up to the next multiple of 32), per layer
+    its input and its gradient (bf16); plus the loss sums."""
+    import ctypes
+    from paper_2503_20605_amd import _lib
+    lib = _lib.load()
+    W = (ctypes.c_int * len(widths))(*widths)
+    size = [lib.iblb_mlp_workspace_bytes(len(widths) - 1, W, b) for b in (32000, 64000)]
+    row = sum(4 * (-(-w // 32) * 32) for w in widths[1:-1]) + 2 * (sum(widths[:-1]) + sum(widths[1:])) + 1
+    assert 0 < size[1] - size[0] <= 32000 * row
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("widths,batch", [([4, 100, 33, 70], 40), ([256, 256, 1000], 33), ([20, 16384], 5), ([1, 1], 1)])
 def test_updated_weights_are_the_ones_that_are_used(widths, batch):
