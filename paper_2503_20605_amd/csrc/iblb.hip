@@ -111,8 +111,18 @@ constexpr int kPlanePad = IBLB_PLANE_PAD;
 // Nodes from which on the 2D node kernel is k_ring2 (see there): its three
 // stages take longer than k_ib_fused2's one, 17.2 against 16.5 us per step of
 // 8 droplets (3 700 nodes), and win from 12 on (5 500 nodes:
-// 20.8 against 21.3; 32: 33.9 against 40.5).
+// 20.8 against 21.3; 32: 33.9 against 40.5).  A lone droplet's k_ib_fused2
+// reads its ring without the droplet's record and is ahead for longer where
+// the nodes are not crowded: up to four nodes per cell of half the box's
+// perimeter, at most kRingMost (k_ib_fused2 / k_ring2, us per step: 512x256
+// 5120 nodes 16.5 / 14.2; 1024x512 5120 17.0 / 17.7, 7168 17.7 / 17.8, 8192
+// 20.8 / 18.0; 2048x1024 5120 33.0 / 35.3, 7168 34.7 / 35.2, 8192 35.7 / 35.6,
+// 16384 43.3 / 36.3; fp16 7168 23.9 / 24.7, 8192 25.8 / 25.2).
 constexpr int kRingNodes = 5120;
+constexpr int kRingMost = 8192;
+int ring_nodes(int n, const iblb_params& p) {
+    return n > 1 ? kRingNodes : std::min(kRingMost, std::max(kRingNodes, 4 * (p.nx + p.ny)));
+}
 
 // Cell budget of a 3D spreading chunk's tap box when the host cuts chunks
 // (see morton_order); the kernel's own limit is kBoxCells.
@@ -251,7 +261,7 @@ bool plan(int n, const iblb_params* P, const int* nn, const int* nt, int storage
     const long long C = L.cells;
     const int N = std::max(L.ntot, 1), T = std::max(L.ttot, 1);
     size_t o = 0;
-    if (L.ntot < kRingNodes) L.nrings = 0;
+    if (L.ntot < ring_nodes(n, P[0])) L.nrings = 0;
     auto take = [&](size_t bytes) { size_t at = o; o = align_up(o + bytes); return at; };
     L.drops = take(sizeof(DropDev) * n);
     L.tiles_lb = take(sizeof(int4) * L.max_tiles);

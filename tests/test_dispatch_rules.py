@@ -3,6 +3,10 @@ the sanitizer build, and what they give against the oracle."""
 import numpy as np
 import pytest
 
+import oracle as o
+import workloads as wl
+from emu import run_case
+from helpers import compare_fields
 from oracle import mlp as ref
 
 
@@ -20,6 +24,24 @@ def _network(widths, batch):
     rng = np.random.default_rng(5)
     return (ref.init_params(widths, 7), rng.uniform(-1, 1, (batch, widths[0])),
             0.3 * rng.standard_normal((batch, widths[-1])))
+
+
+@pytest.mark.parametrize("nx,ny,nodes,ring", [(24, 16, [5119], False), (24, 16, [5120], True),
+                                              (1400, 8, [5631], False), (1400, 8, [5632], True),
+                                              (3000, 8, [8191], False), (3000, 8, [8192], True),
+                                              (1400, 8, [5100, 19], False), (1400, 8, [5100, 20], True)])
+def test_node_kernel_2d(nx, ny, nodes, ring):
+    """k_ib_fused2 for few nodes, k_ring2 for many (a lone outline in a large
+    box: later)."""
+    p = wl.Params(dim=2, nx=nx, ny=ny, tau=0.9, sigma=0.005, theta_eq_deg=80.0, xi=2.0)
+    qs = [wl.cap_polygon(4.0, 90.0, 2.0, n, nx / 2) for n in nodes]
+    launches = []
+    out = run_case([p] * len(nodes), qs, steps=(2,), launches=launches)
+    assert any("k_ring2" in k for k in launches) == ring
+    assert any("k_ib_fused2" in k for k in launches) != ring
+    r = o.run(p, qs[-1], 2)
+    drho, du, dq = compare_fields(out[-1], r, 2, f"nodes {nodes}")
+    assert drho <= 1e-6 and du <= 1e-5 and dq <= 1e-7
 
 
 # narrow networks: many outputs for few rows, and a single layer, train layer
