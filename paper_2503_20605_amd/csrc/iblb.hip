@@ -823,7 +823,7 @@ void launch_diag_d(iblb_ctx* c, bool cells = true) {
     const int4* blocks = c->at<int4>(c->L.blocks);
     double* part = c->at<double>(c->L.part);
     const double* sums = cells ? (const double*)c->at<double>(c->L.partials) : nullptr;
-    if (c->L.most_blocks <= kFewBlocks) {
+    if (c->L.most_blocks <= few_blocks_diag<DIM>()) {
         hipLaunchKernelGGL(k_diag_one<DIM>, dim3(c->n), dim3(kBlock), 0, c->stream, D, A, sums,
                            c->at<DiagDev>(c->L.diag));
         return;
@@ -846,7 +846,7 @@ void launch_contact(iblb_ctx* c, int d, double z_cut, double flat_tol, double* o
     const int4* blocks = c->at<int4>(c->L.blocks) + c->drops[d].blk_off;
     double* part = c->at<double>(c->L.part);
     const dim3 grid(c->drops[d].n_blks), block(kBlock);
-    if (c->drops[d].n_blks <= kFewBlocks) {
+    if (c->drops[d].n_blks <= few_blocks_contact<DIM>()) {
         hipLaunchKernelGGL(k_contact_one<DIM>, dim3(1), block, 0, c->stream, D, d, A, z_cut, flat_tol, out);
         return;
     }

@@ -2461,10 +2461,16 @@ __global__ __launch_bounds__(kFinalBlock) void k_diag_final(const DropDev* __res
     diag_final<DIM, kFinalBlock>(D, partials, chunk_of(D, make_int4(0, 0, 0, 0), part), out + blockIdx.x);
 }
 // All of it by one workgroup per droplet that strides over the whole
-// interface: for small ones (at most kFewBlocks chunks), where the launches
-// would take longer than the work (329x234, 625 nodes, diagnostics + contact
-// radius: 86 us against 93.6 us with the launches above).
-constexpr int kFewBlocks = 4;
+// interface: for small ones, where the launches would take longer than the
+// work.  Up to how many chunks, per dimension (us per call, one workgroup /
+// launches): diagnostics 2D 1200 nodes (5 chunks) 61.1 / 61.5, 1700 (7) 62.4 /
+// 61.8, 8000 79.8 / 61.4; 3D 362 vertices (2) 76.9 / 78.0, 642 (3) 84.6 / 78.3,
+// 4002 177 / 81; contact radius 2D 4000 (16) 34.0 / 36.2, 5000 (20) 35.6 / 36.4,
+// 6000 (24) 36.9 / 36.3; 3D 1212 (5) 41.0 / 41.3, 1442 (6) 42.7 / 41.6.
+template <int DIM>
+constexpr int few_blocks_diag() { return DIM == 2 ? 5 : 2; }
+template <int DIM>
+constexpr int few_blocks_contact() { return DIM == 2 ? 20 : 5; }
 template <int DIM>
 __global__ __launch_bounds__(kBlock) void k_diag_one(const DropDev* __restrict__ drops, NodeArrays A,
                                                      const double* __restrict__ partials,

@@ -44,6 +44,32 @@ def test_node_kernel_2d(nx, ny, nodes, ring):
     assert drho <= 1e-6 and du <= 1e-5 and dq <= 1e-7
 
 
+# outline nodes or mesh frequency; diagnostics and contact radius by one
+# workgroup or by several launches
+@pytest.mark.parametrize("dim,size,diag_one,contact_one", [(2, 1280, True, True), (2, 1281, False, True),
+                                                           (2, 5120, False, True), (2, 5121, False, False),
+                                                           (3, 7, True, True), (3, 8, False, True),
+                                                           (3, 11, False, True), (3, 12, False, False)])
+def test_diagnostics_of_small_interfaces(dim, size, diag_one, contact_one):
+    launches = []
+    if dim == 2:
+        p = wl.Params(dim=2, nx=24, ny=16, tau=0.9, sigma=0.005, theta_eq_deg=80.0, xi=2.0)
+        q, t = wl.cap_polygon(6.0, 90.0, 2.0, size, 12.0), None
+    else:
+        p = wl.Params(dim=3, nx=20, ny=20, nz=12, bc=(0, 0, 1), tau=0.9, sigma=0.005, theta_eq_deg=80.0, xi=2.0)
+        q, t = wl.cap_mesh(6.0, 90.0, 2.0, size, (10.0, 10.0))
+    out = run_case([p], [q], [t], steps=(1,), contact=(3.0, 0.05), launches=launches)[0]
+    assert any("k_diag_one" in k for k in launches) == diag_one
+    assert any("k_diag_part" in k for k in launches) != diag_one
+    assert any("k_contact_one" in k for k in launches) == contact_one
+    assert any("k_contact_part" in k for k in launches) != contact_one
+    # double precision on both sides, only the order of the sums differs
+    want = o.contact_radius_2d(out["q"], 3.0) if dim == 2 else o.contact_radius_3d(out["q"], t, 3.0)
+    assert abs(out["contact"][0] - want) <= 1e-11 * want
+    want = o.volume_2d(out["q"]) if dim == 2 else o.volume_3d(out["q"], t)
+    assert abs(out["diag"]["volume"] - want) <= 1e-11 * want
+
+
 # narrow networks: many outputs for few rows, and a single layer, train layer
 # by layer; the others in one launch
 TRAINING = [([16, 24], 5, False), ([4, 24, 12000], 3, False), ([4, 24, 8000], 3, True), ([4, 16, 16, 70], 33, True),
