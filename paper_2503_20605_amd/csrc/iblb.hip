@@ -728,12 +728,12 @@ void launch_pop_io(iblb_ctx* c, int d, const double* in, double* out) {
     T* f = c->at<T>(c->cur ? c->L.f1 : c->L.f0) + c->drops[d].f_off;
     const DropDev& D = c->drops[d];
     const int nxy = D.nx * D.ny;
-    const dim3 grid(ceil_div(nxy, kPopCells), std::min(D.nz, 65535), c->Q);
+    const dim3 grid(ceil_div(D.ncell, kPopCells), c->Q);
     if (in)
-        hipLaunchKernelGGL(k_pop_write<S>, grid, dim3(kBlock), 0, c->stream, f, D.ncell, D.fst, nxy, D.ppl, D.nz, in);
+        hipLaunchKernelGGL(k_pop_write<S>, grid, dim3(kBlock), 0, c->stream, f, D.ncell, D.fst, nxy, D.ppl, in);
     else
         hipLaunchKernelGGL(k_pop_read<S>, grid, dim3(kBlock), 0, c->stream, (const T*)f, D.ncell, D.fst, nxy, D.ppl,
-                           D.nz, out);
+                           out);
 }
 
 int pop_io(iblb_ctx* c, int d, const double* in, double* out) {

@@ -2045,42 +2045,61 @@ __global__ void k_init_eq(typename Codec<S>::T* __restrict__ f, int ncell, int f
 
 // Dense [Q][ncell] doubles on the caller's side, population arrays fst
 // elements apart in the workspace, their planes ppl elements apart: one
-// workgroup per kPopCells cells of plane blockIdx.y (then every gridDim.y-th
-// plane) of population blockIdx.z, four elements per lane in flight.  HBM
-// bound; with one lane per element and its index divided by the cell count
-// in 64 bits it was not (240x240x130 fp16: 430 us to write and 464 us to
-// read; 285 and 247 us = 5.0 and 5.8 TB/s so).
+// workgroup per kPopCells cells of population blockIdx.y, four elements per
+// lane in flight.  HBM bound; with one lane per element and its index divided
+// by the cell count in 64 bits it was not.  A lane divides once, by the plane's
+// cells, and steps on from there (a workgroup per plane instead left most
+// lanes idle on small planes).  us per call to write / read (64-bit divisions;
+// workgroup per plane; now): 240x240x130 fp16 413 / 487; 299 / 244; 316 / 234,
+// 32x32x4096 fp32 222 / 280; 182 / 173; 186 / 174, 16x16x10000 fp32 146 / 182;
+// 139 / 103; 114 / 97, 4x4x100000 fp32 106 / 119; 587 / 562; 88 / 98.
 constexpr int kPopCells = 4 * kBlock;
+// The cells c0, c0 + kBlock, ... of a lane: their places in a population array.
+struct PopPlaces {
+    int at[4];
+    __device__ __forceinline__ PopPlaces(int c0, int nxy, int ppl) {
+        const int dz = kBlock / nxy, dr = kBlock - dz * nxy;  // (the same for all lanes)
+        int z = c0 / nxy, r = c0 - z * nxy;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            at[u] = z * ppl + r;
+            z += dz;
+            r += dr;
+            if (r >= nxy) {
+                r -= nxy;
+                ++z;
+            }
+        }
+    }
+};
 template <int S>
 __global__ __launch_bounds__(kBlock) void k_pop_write(typename Codec<S>::T* __restrict__ f, int ncell, int fst,
-                                                      int nxy, int ppl, int nz, const double* __restrict__ src) {
-    const int i = blockIdx.z, c0 = blockIdx.x * kPopCells + threadIdx.x;
-    for (int z = blockIdx.y; z < nz; z += gridDim.y) {
-        const double* __restrict__ s = src + (long long)i * ncell + (long long)z * nxy;
-        typename Codec<S>::T* __restrict__ d = f + (long long)i * fst + (long long)z * ppl;
-        double v[4];
+                                                      int nxy, int ppl, const double* __restrict__ src) {
+    const int i = blockIdx.y, c0 = blockIdx.x * kPopCells + threadIdx.x;
+    const double* __restrict__ s = src + (long long)i * ncell + c0;
+    typename Codec<S>::T* __restrict__ d = f + (long long)i * fst;
+    const PopPlaces P(c0, nxy, ppl);
+    double v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = c0 + u * kBlock < nxy ? __builtin_nontemporal_load(s + c0 + u * kBlock) : 0.0;
+    for (int u = 0; u < 4; ++u) v[u] = c0 + u * kBlock < ncell ? __builtin_nontemporal_load(s + u * kBlock) : 0.0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (c0 + u * kBlock < nxy) d[c0 + u * kBlock] = Codec<S>::from_double(v[u]);
-    }
+    for (int u = 0; u < 4; ++u)
+        if (c0 + u * kBlock < ncell) d[P.at[u]] = Codec<S>::from_double(v[u]);
 }
 
 template <int S>
 __global__ __launch_bounds__(kBlock) void k_pop_read(const typename Codec<S>::T* __restrict__ f, int ncell, int fst,
-                                                     int nxy, int ppl, int nz, double* __restrict__ dst) {
-    const int i = blockIdx.z, c0 = blockIdx.x * kPopCells + threadIdx.x;
-    for (int z = blockIdx.y; z < nz; z += gridDim.y) {
-        const typename Codec<S>::T* __restrict__ s = f + (long long)i * fst + (long long)z * ppl;
-        double* __restrict__ d = dst + (long long)i * ncell + (long long)z * nxy;
-        typename Codec<S>::T v[4];
+                                                     int nxy, int ppl, double* __restrict__ dst) {
+    const int i = blockIdx.y, c0 = blockIdx.x * kPopCells + threadIdx.x;
+    const typename Codec<S>::T* __restrict__ s = f + (long long)i * fst;
+    double* __restrict__ d = dst + (long long)i * ncell + c0;
+    const PopPlaces P(c0, nxy, ppl);
+    typename Codec<S>::T v[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = s[c0 + u * kBlock < nxy ? c0 + u * kBlock : 0];
+    for (int u = 0; u < 4; ++u) v[u] = s[c0 + u * kBlock < ncell ? P.at[u] : 0];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (c0 + u * kBlock < nxy) __builtin_nontemporal_store(Codec<S>::to_double(v[u]), d + c0 + u * kBlock);
-    }
+    for (int u = 0; u < 4; ++u)
+        if (c0 + u * kBlock < ncell) __builtin_nontemporal_store(Codec<S>::to_double(v[u]), d + u * kBlock);
 }
 
 // Streaming copy used to measure the attainable HBM bandwidth of the device:

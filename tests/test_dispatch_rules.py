@@ -70,6 +70,19 @@ def test_diagnostics_of_small_interfaces(dim, size, diag_one, contact_one):
     assert abs(out["diag"]["volume"] - want) <= 1e-11 * want
 
 
+@pytest.mark.parametrize("nx,ny,nz", [(4, 4, 300), (3, 5, 200), (1, 1, 600), (16, 16, 9), (17, 16, 7), (40, 30, 5)])
+def test_population_exchange_over_planes(nx, ny, nz):
+    """Planes of less than a workgroup's lanes, of as many, of more: one step
+    of the fluid from populations that differ in every element."""
+    p = wl.Params(dim=3, nx=nx, ny=ny, nz=nz, bc=(0, 0, 1), tau=0.9, wetting=False)
+    f = np.random.default_rng(8).uniform(-1e-3, 1e-3, (19, nz, ny, nx))
+    out = run_case([p], steps=(1,), f0dev=[f])[0]
+    w = o.lattice(3)[1][:, None, None, None]
+    r = o.run(p, None, 1, f0=f + w)
+    # fp32: the rounding of the input and of the collision
+    assert np.max(np.abs(out["fdev"] - (r["f"] - w))) <= 1e-8
+
+
 # narrow networks: many outputs for few rows, and a single layer, train layer
 # by layer; the others in one launch
 TRAINING = [([16, 24], 5, False), ([4, 24, 12000], 3, False), ([4, 24, 8000], 3, True), ([4, 16, 16, 70], 33, True),
