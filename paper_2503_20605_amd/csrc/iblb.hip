@@ -727,13 +727,16 @@ void launch_pop_io(iblb_ctx* c, int d, const double* in, double* out) {
     using T = typename Codec<S>::T;
     T* f = c->at<T>(c->cur ? c->L.f1 : c->L.f0) + c->drops[d].f_off;
     const DropDev& D = c->drops[d];
-    const int nxy = D.nx * D.ny;
-    const dim3 grid(ceil_div(D.ncell, kPopCells), c->Q);
+    const PopPlanes P(D.nx * D.ny, D.ppl);
+    const bool flat = P.nxy < kPopCells;
+    const int nz = flat ? 1 : D.nz;  // rounds over planes
+    const dim3 grid(ceil_div(flat ? D.ncell : P.nxy, kPopCells), std::min(nz, 65535), c->Q);
     if (in)
-        hipLaunchKernelGGL(k_pop_write<S>, grid, dim3(kBlock), 0, c->stream, f, D.ncell, D.fst, nxy, D.ppl, in);
+        hipLaunchKernelGGL((flat ? k_pop_write<S, true> : k_pop_write<S, false>), grid, dim3(kBlock), 0, c->stream, f,
+                           D.ncell, D.fst, nz, P, in);
     else
-        hipLaunchKernelGGL(k_pop_read<S>, grid, dim3(kBlock), 0, c->stream, (const T*)f, D.ncell, D.fst, nxy, D.ppl,
-                           out);
+        hipLaunchKernelGGL((flat ? k_pop_read<S, true> : k_pop_read<S, false>), grid, dim3(kBlock), 0, c->stream,
+                           (const T*)f, D.ncell, D.fst, nz, P, out);
 }
 
 int pop_io(iblb_ctx* c, int d, const double* in, double* out) {

@@ -2045,21 +2045,29 @@ __global__ void k_init_eq(typename Codec<S>::T* __restrict__ f, int ncell, int f
 
 // Dense [Q][ncell] doubles on the caller's side, population arrays fst
 // elements apart in the workspace, their planes ppl elements apart: one
-// workgroup per kPopCells cells of population blockIdx.y, four elements per
+// workgroup per kPopCells cells of population blockIdx.z, four elements per
 // lane in flight.  HBM bound; with one lane per element and its index divided
-// by the cell count in 64 bits it was not.  A lane divides once, by the plane's
-// cells, and steps on from there (a workgroup per plane instead left most
-// lanes idle on small planes).  us per call to write / read (64-bit divisions;
-// workgroup per plane; now): 240x240x130 fp16 413 / 487; 299 / 244; 316 / 234,
-// 32x32x4096 fp32 222 / 280; 182 / 173; 186 / 174, 16x16x10000 fp32 146 / 182;
-// 139 / 103; 114 / 97, 4x4x100000 fp32 106 / 119; 587 / 562; 88 / 98.
+// by the cell count in 64 bits it was not.  The cells are those of plane
+// blockIdx.y (then every gridDim.y-th plane), or, where a plane has fewer than
+// kPopCells and most lanes would be idle, of the box (FLAT).  us per call to
+// write / read (64-bit divisions; by planes; by the box): 240x240x130 fp16 413
+// / 487; 302 / 248; 310 / 311, 32x32x4096 fp16 240 / 281; 175 / 126; 183 / 126,
+// 16x16x10000 146 / 182; 139 / 106; 113 / 98, 4x4x100000 106 / 119; 587 / 562;
+// 89 / 97.
 constexpr int kPopCells = 4 * kBlock;
-// The cells c0, c0 + kBlock, ... of a lane: their places in a population array.
-struct PopPlaces {
-    int at[4];
-    __device__ __forceinline__ PopPlaces(int c0, int nxy, int ppl) {
-        const int dz = kBlock / nxy, dr = kBlock - dz * nxy;  // (the same for all lanes)
-        int z = c0 / nxy, r = c0 - z * nxy;
+// Cell c of a box: plane c / nxy = c mul >> shift, exact for c < 2^28 (boxes stay
+// below: Q cells < 2^31) as mul = ceil(2^shift / nxy), shift = 28 + ceil(log2 nxy).
+struct PopPlanes {
+    int nxy, ppl, dz, dr;  // kBlock cells on: dz planes and dr cells
+    unsigned mul;
+    int shift;
+    PopPlanes(int cells, int pitch) : nxy(cells), ppl(pitch), dz(kBlock / cells), dr(kBlock % cells), shift(28) {
+        while ((1LL << (shift - 28)) < nxy) ++shift;
+        mul = (unsigned)(((1ULL << shift) + nxy - 1) / nxy);
+    }
+    // the places of cells c0, c0 + kBlock, ... in a population array
+    __device__ __forceinline__ void places(int c0, int (&at)[4]) const {
+        int z = (int)((unsigned long long)c0 * mul >> shift), r = c0 - z * nxy;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             at[u] = z * ppl + r;
@@ -2072,34 +2080,40 @@ struct PopPlaces {
         }
     }
 };
-template <int S>
+template <int S, bool FLAT>
 __global__ __launch_bounds__(kBlock) void k_pop_write(typename Codec<S>::T* __restrict__ f, int ncell, int fst,
-                                                      int nxy, int ppl, const double* __restrict__ src) {
-    const int i = blockIdx.y, c0 = blockIdx.x * kPopCells + threadIdx.x;
-    const double* __restrict__ s = src + (long long)i * ncell + c0;
-    typename Codec<S>::T* __restrict__ d = f + (long long)i * fst;
-    const PopPlaces P(c0, nxy, ppl);
-    double v[4];
+                                                      int nz, PopPlanes P, const double* __restrict__ src) {
+    const int i = blockIdx.z, c0 = blockIdx.x * kPopCells + threadIdx.x, n = FLAT ? ncell : P.nxy;
+    for (int z = blockIdx.y; z < nz; z += gridDim.y) {
+        const double* __restrict__ s = src + (long long)i * ncell + (long long)z * P.nxy;
+        typename Codec<S>::T* __restrict__ d = f + (long long)i * fst + (long long)z * P.ppl;
+        int at[4];
+        if (FLAT) P.places(c0, at);
+        double v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = c0 + u * kBlock < ncell ? __builtin_nontemporal_load(s + u * kBlock) : 0.0;
+        for (int u = 0; u < 4; ++u) v[u] = c0 + u * kBlock < n ? __builtin_nontemporal_load(s + c0 + u * kBlock) : 0.0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (c0 + u * kBlock < ncell) d[P.at[u]] = Codec<S>::from_double(v[u]);
+        for (int u = 0; u < 4; ++u)
+            if (c0 + u * kBlock < n) d[FLAT ? at[u] : c0 + u * kBlock] = Codec<S>::from_double(v[u]);
+    }
 }
 
-template <int S>
+template <int S, bool FLAT>
 __global__ __launch_bounds__(kBlock) void k_pop_read(const typename Codec<S>::T* __restrict__ f, int ncell, int fst,
-                                                     int nxy, int ppl, double* __restrict__ dst) {
-    const int i = blockIdx.y, c0 = blockIdx.x * kPopCells + threadIdx.x;
-    const typename Codec<S>::T* __restrict__ s = f + (long long)i * fst;
-    double* __restrict__ d = dst + (long long)i * ncell + c0;
-    const PopPlaces P(c0, nxy, ppl);
-    typename Codec<S>::T v[4];
+                                                     int nz, PopPlanes P, double* __restrict__ dst) {
+    const int i = blockIdx.z, c0 = blockIdx.x * kPopCells + threadIdx.x, n = FLAT ? ncell : P.nxy;
+    for (int z = blockIdx.y; z < nz; z += gridDim.y) {
+        const typename Codec<S>::T* __restrict__ s = f + (long long)i * fst + (long long)z * P.ppl;
+        double* __restrict__ d = dst + (long long)i * ncell + (long long)z * P.nxy;
+        int at[4];
+        if (FLAT) P.places(c0, at);
+        typename Codec<S>::T v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = s[c0 + u * kBlock < ncell ? P.at[u] : 0];
+        for (int u = 0; u < 4; ++u) v[u] = s[c0 + u * kBlock < n ? (FLAT ? at[u] : c0 + u * kBlock) : 0];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-        if (c0 + u * kBlock < ncell) __builtin_nontemporal_store(Codec<S>::to_double(v[u]), d + u * kBlock);
+        for (int u = 0; u < 4; ++u)
+            if (c0 + u * kBlock < n) __builtin_nontemporal_store(Codec<S>::to_double(v[u]), d + c0 + u * kBlock);
+    }
 }
 
 // Streaming copy used to measure the attainable HBM bandwidth of the device:
