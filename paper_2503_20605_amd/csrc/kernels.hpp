@@ -149,6 +149,30 @@ __device__ __forceinline__ void wanted(T v, U... u) {
     wanted(u...);
 }
 
+// v (a lane's own), as a value that the compiler cannot form ahead of the
+// place of the call; opaque_uniform: v the same for all lanes.
+__device__ __forceinline__ int opaque(int v) {
+#ifdef __AMDGCN__
+    __asm__ volatile("" : "+v"(v));
+#endif
+    return v;
+}
+__device__ __forceinline__ int opaque_uniform(int v) {
+#ifdef __AMDGCN__
+    __asm__ volatile("" : "+s"(v));
+#endif
+    return v;
+}
+
+// Keeps the narrowing of v to fp16 a rounding of its own (the compiler would
+// merge it into the fma before it).
+__device__ __forceinline__ float unfused(float v) {
+#ifdef __AMDGCN__
+    __asm__("" : "+v"(v));
+#endif
+    return v;
+}
+
 // One cell's collision in deviation form (eqs. LBE, f^eq, S_i,
 // hydro_var1/2), in two parts so that callers can store each population as
 // soon as it is relaxed: the constructor takes the streamed deviations
@@ -168,15 +192,6 @@ __device__ __forceinline__ void wanted(T v, U... u) {
 // fma that takes them.  With the record of the droplet read in one batch
 // (k_lb): 1024x512 fp32 15.7 -> 13.9 us per coupled step, the batch 245 ->
 // 236 us.
-// Keeps the narrowing of v to fp16 a rounding of its own (the compiler would
-// merge it into the fma before it).
-__device__ __forceinline__ float unfused(float v) {
-#ifdef __AMDGCN__
-    __asm__("" : "+v"(v));
-#endif
-    return v;
-}
-
 template <int DIM, int S>
 struct Moments {
     float drho, rho, inv, jx, jy, jz, ux, uy, uz, usq, Fx, Fy, Fz;
@@ -1488,10 +1503,14 @@ __global__ __launch_bounds__(kSpreadBlock, kSpreadWaves) void k_spread3(const Dr
     const int run = measure() ? kChunk : kRun;
     unsigned long long* __restrict__ Fq = Fq_all + 3LL * D.c_off;
     bool fine = true;
-    const int k = t & 63;  // tap of this lane; one vertex per wavefront at a time
-    const int kx = k & 3, ky = (k >> 2) & 3, kz = k >> 4;
     for (int first = 0; first < count; first += run) {
         const int last = first + run < count ? first + run : count;
+        // (what the compiler would form ahead of the loop, reciprocals and
+        // addresses of its later parts, delays the chunks of one round: 80x80x60
+        // 34.0 against 33.9 us per step)
+        const int nx = opaque_uniform(D.nx), ny = opaque_uniform(D.ny), nz = opaque_uniform(D.nz);
+        const int t = opaque(threadIdx.x), k = t & 63;  // tap of this lane; one vertex per wavefront at a time
+        const int kx = k & 3, ky = (k >> 2) & 3, kz = k >> 4;
         if (run < kChunk) {  // the run's own box
             __syncthreads();
             if (t < 3) {
@@ -1535,7 +1554,7 @@ __global__ __launch_bounds__(kSpreadBlock, kSpreadWaves) void k_spread3(const Dr
                 }
                 touched[c] = 1;
             } else {
-                const int row = gz * D.ny + gy, cell = row * D.nx + gx;
+                const int row = gz * ny + gy, cell = row * nx + gx;
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
                     const float val = sph[v][a] * w;
@@ -1566,9 +1585,9 @@ __global__ __launch_bounds__(kSpreadBlock, kSpreadWaves) void k_spread3(const Dr
             const int r = (int)(((float)c + 0.5f) * rx), cz = (int)(((float)r + 0.5f) * ry);
             const int cx = c - r * ex, cy = r - cz * ey;
             // a touched cell received a fluid tap, so none of these is -1
-            const int gx = tap_index(lo[0], cx, D.nx, D.bcx), gy = tap_index(lo[1], cy, D.ny, D.bcy),
-                      gz = tap_index(lo[2], cz, D.nz, D.bcz);
-            const int row = gz * D.ny + gy, cell = row * D.nx + gx;
+            const int gx = tap_index(lo[0], cx, nx, D.bcx), gy = tap_index(lo[1], cy, ny, D.bcy),
+                      gz = tap_index(lo[2], cz, nz, D.bcz);
+            const int row = gz * ny + gy, cell = row * nx + gx;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const unsigned long long v = box[a * kBoxCells + c];
