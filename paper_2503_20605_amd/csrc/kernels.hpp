@@ -190,8 +190,10 @@ __device__ __forceinline__ float unfused(float v) {
 // off), so that the result does not depend on the kernel that the code is
 // inlined into: the products of the sums below are rounded once, inside the
 // fma that takes them.  With the record of the droplet read in one batch
-// (k_lb): 1024x512 fp32 15.7 -> 13.9 us per coupled step, the batch 245 ->
-// 236 us.
+// (k_lb), kernel trace of 1024x512 fp32: 7.3-7.6 -> 6.5-6.9 us per launch with
+// plain stores, 10.3 -> 8.7 with non-temporal ones and the late band flag (a
+// coupled step of it 14.0 -> 13.8 and 16.6 -> 15.4); the batch's step 245 -> 236
+// us.
 template <int DIM, int S>
 struct Moments {
     float drho, rho, inv, jx, jy, jz, ux, uy, uz, usq, Fx, Fy, Fz;
