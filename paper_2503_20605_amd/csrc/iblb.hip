@@ -1057,8 +1057,8 @@ void morton_order(const double* pos, int N, int off, std::vector<int>& perm, int
     for (int k = 0; k < N; ++k) perm[k] = off + key[k].second;
     // Cut the order into chunks of at most kChunk vertices whose taps fit a
     // box of kChunkBudget cells (below the kernel's kBoxCells, so that the
-    // vertices can move a little before a chunk overflows into the direct
-    // path).
+    // vertices can move a little before a chunk outgrows it and is taken in
+    // runs).
     // (in doubles: any finite position is accepted, and the product of far
     // extents has to stay a large number)
     constexpr double kChunkBudget = IBLB_CHUNK_BUDGET;

@@ -611,8 +611,9 @@ __global__ void k_zero_f32(float* __restrict__ x, long long n) {
 
 // Adam (Kingma & Ba) on the fp32 master copy; bc1 = 1 - beta1^t,
 // bc2 = 1 - beta2^t.  Writes the bf16 copy used by the products and, with
-// PACK, its packed form (element by element: a launch of k_pack after every
-// step took 20 us).
+// PACK, its packed form, element by element (a launch of k_pack after every
+// step instead: 16-2048 69 us per training step against 46, 4-256-256-256-1280
+// 142 against 140).
 template <bool PACK>
 __global__ void k_adam(float* __restrict__ w, uint16_t* __restrict__ wb, const float* __restrict__ g,
                        float* __restrict__ m, float* __restrict__ v, long long n, float lr,
