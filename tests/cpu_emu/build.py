@@ -11,7 +11,7 @@ SRCS = [os.path.join(ROOT, "paper_2503_20605_amd", "csrc", f) for f in ("iblb.hi
 OUT = os.path.join(HERE, "iblb_emu_driver")
 # Second build whose host-side chunking ignores the box budget (plain runs
 # of the chunk size), so that spreading chunks overflow the kernel's LDS box
-# and take its direct-atomic path.
+# and go through it in runs or add straight to memory.
 OUT_DIRECT = os.path.join(HERE, "iblb_emu_driver_direct")
 CXX = "/opt/rocm/llvm/bin/clang++"
 
